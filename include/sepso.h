@@ -149,9 +149,9 @@ typedef struct sepso_batch sepso_batch;
  * poly_ptr[0] = 0, poly_ptr[n_polys] = n_vert), verts (n_vert (x, y)
  * pairs), ends (4 floats: start x, y, target x, y), paths (n_paths x 2W).
  * Device outputs: f, L (n_paths floats), Q (n_paths int32).  The workspace
- * (size from sepso_fitness_workspace_bytes, 256-byte aligned) holds the
- * edge records and per-segment partial results; it is free again when the
- * work has completed.  Asynchronous on stream (NULL = the default stream);
+ * (size from sepso_fitness_workspace_bytes, 256-byte aligned) belongs to the
+ * call until its work has completed; the present kernel keeps its working
+ * data on chip and leaves it untouched.  Asynchronous on stream (NULL = the default stream);
  * n_paths = 0 launches nothing.  1 <= waypoints <= 64, beta >= 1, alpha
  * finite, n_paths * (W + 1) < 2^31, else SEPSO_E_ARG; a workspace that is
  * too small gives SEPSO_E_NOMEM; a launch failure gives SEPSO_E_HIP. */
@@ -165,15 +165,12 @@ sepso_status sepso_fitness(int32_t n_polys, int32_t n_vert, const int32_t* d_pol
 
 /* sepso_fitness without a workspace, for callers that cannot allocate device
  * memory (code under HIP graph capture, tight serving loops, harnesses that
- * forbid hipMalloc): the edge records and per-segment partial results live
- * in a fixed 8 MiB device array that the library holds on each GPU it runs
- * on until the process ends.  The call allocates nothing (no hipMalloc,
- * hipFree or allocating library routine).  Requests whose workspace
- * (sepso_fitness_workspace_bytes) would exceed 8 MiB give SEPSO_E_ARG.
- * Every call on one GPU shares that GPU's array: calls that overlap on one
- * GPU (different streams or threads, work still in flight) race; calls
- * ordered on one stream do not.  Same arguments, results and errors as
- * sepso_fitness otherwise. */
+ * forbid hipMalloc).  The call allocates nothing (no hipMalloc, hipFree or
+ * allocating library routine) and shares no memory with other calls, so
+ * calls on different streams or threads may overlap.  Requests whose
+ * workspace (sepso_fitness_workspace_bytes) would exceed 8 MiB give
+ * SEPSO_E_ARG.  Same arguments, results and errors as sepso_fitness
+ * otherwise. */
 sepso_status sepso_fitness_noalloc(int32_t n_polys, int32_t n_vert, const int32_t* d_poly_ptr,
                                    const float* d_verts, const float* d_ends, const float* d_paths,
                                    int32_t n_paths, int32_t waypoints, float alpha, int32_t beta,

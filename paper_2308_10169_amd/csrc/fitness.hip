@@ -1,15 +1,8 @@
 // Path fitness of given paths on a polygonal map (Eq.(11)-(13)): polyline
 // length L over [start, waypoints, target], Q = proper crossings of the W+1
 // segments with every polygon edge, F = L + alpha * Q^beta.  Stateless: the
-// caller passes device inputs and outputs and a device workspace.
-//
-//   fit_edges_kernel -- one thread per vertex: the edge from it to the next
-//                       vertex of its polygon (the last closes the polygon);
-//   fit_seg_kernel   -- one thread per (path, segment): the segment's length
-//                       and its proper crossings with every edge (records
-//                       staged through LDS), as per-segment partial results;
-//   fit_sum_kernel   -- one thread per path: L and Q summed in segment order
-//                       (deterministic), F.
+// caller passes device inputs and outputs; one launch, fit_kernel, and no
+// device memory besides.
 //
 // Orientation arithmetic: a segment p -> q is kept as (dx, dy) and the line
 // constant nc = dy*p.x - dx*p.y, so orient(p, q, v) = dx*v.y - dy*v.x + nc
@@ -18,8 +11,9 @@
 // signs; touching and collinear contacts never count.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+#include <cfloat>
 #include <cmath>
-#include <mutex>
 
 #include "../../include/sepso.h"
 #include "internal.h"
@@ -27,141 +21,324 @@
 namespace sepso {
 namespace {
 
-constexpr int kFitThreads = 256;
-constexpr int kFitStage = 512;  // edge records per LDS pass (16 KiB)
+constexpr int kFitVerts = 2560;  // vertices staged in LDS per pass (20 KiB)
+constexpr int kFitPolys = 768;   // polygons per pass (boxes 12 KiB, offsets 3 KiB)
+constexpr int kFitLong = 32;     // a polygon of more edges is walked by the whole wave
+constexpr int kFitMaxThreads = 512;
 
-struct FitEdge {
-  float ax, ay, bx, by;  // end points
-  float ex, ey, ce, pad; // b - a and the line constant
+// LDS of one block: staged vertices, polygon boxes and offsets, the long
+// polygons' list and its length, the block's path points with the crossings
+// and the length of the segment that starts at each, and a queue per wave.
+// At most 64 KiB (K * threads <= 1024, so ppr * (W + 2) <= 1536).
+struct FitLds {
+  int verts, polys, longs;                        // capacities
+  int box, ptr, lng, pts, cross, len, queue, bytes;  // byte offsets (vertices at 0)
 };
-static_assert(sizeof(FitEdge) == 32, "FitEdge is 32 bytes");
 
-__global__ __launch_bounds__(kFitThreads) void fit_edges_kernel(int n_polys, const int32_t* pptr,
-                                                                const float* verts, int n_vert,
-                                                                FitEdge* out) {
-  const int j = blockIdx.x * kFitThreads + threadIdx.x;
-  if (j >= n_vert) return;
-  // polygon q with pptr[q] <= j < pptr[q + 1] (binary search; q stays in
-  // [0, n_polys) whatever the offsets hold)
-  int lo = 0, hi = n_polys;
-  while (hi - lo > 1) {
-    const int mid = (lo + hi) >> 1;
-    if (pptr[mid] <= j)
-      lo = mid;
-    else
-      hi = mid;
-  }
-  int nx = j + 1 < pptr[lo + 1] ? j + 1 : pptr[lo];
-  if (nx < 0 || nx >= n_vert) nx = j;  // malformed offsets: a zero-length edge, no access outside
-  FitEdge r;
-  r.ax = verts[2 * j];
-  r.ay = verts[2 * j + 1];
-  r.bx = verts[2 * nx];
-  r.by = verts[2 * nx + 1];
-  r.ex = r.bx - r.ax;
-  r.ey = r.by - r.ay;
-  r.ce = fmaf(r.ex, r.ay, -(r.ey * r.ax));
-  r.pad = 0.f;
-  out[j] = r;
+__host__ __device__ inline FitLds fit_lds(int n_polys, int n_vert, int threads, int n_pts) {
+  FitLds l{};
+  l.verts = n_vert < kFitVerts ? (n_vert + 1) & ~1 : kFitVerts;  // 16-byte aligned boxes after them
+  l.polys = n_polys < kFitPolys ? n_polys : kFitPolys;
+  l.longs = kFitVerts / kFitLong < l.polys ? kFitVerts / kFitLong : l.polys;
+  l.box = 8 * l.verts;
+  l.ptr = l.box + 16 * l.polys;
+  l.lng = l.ptr + 4 * (l.polys + 1);
+  l.pts = (l.lng + 4 * (l.longs + 1) + 7) & ~7;
+  l.cross = l.pts + 8 * n_pts;
+  l.len = l.cross + 4 * n_pts;
+  l.queue = l.len + 4 * n_pts;
+  l.bytes = l.queue + 8 * threads;  // 128 words per wave
+  return l;
 }
 
 __device__ __forceinline__ bool opposite(float a, float b) {
   return (a < 0.f && b > 0.f) || (a > 0.f && b < 0.f);
 }
 
-__global__ __launch_bounds__(kFitThreads) void fit_seg_kernel(const FitEdge* edges, int n_edges,
-                                                              const float* ends, const float* paths,
-                                                              int n_seg, int W, int32_t* seg_q,
-                                                              float* seg_l) {
-  __shared__ FitEdge s_e[kFitStage];
-  const int t = threadIdx.x;
-  const int i = blockIdx.x * kFitThreads + t;
-  const bool active = i < n_seg;
-  const int S = W + 1;  // segments per path
-  const int path = active ? i / S : 0, s = active ? i - path * S : 0;
-  const float* x = paths + (int64_t)path * 2 * W;
-  // points s and s + 1 of [start, w_1..w_W, target]
-  auto point = [&](int k, float& px, float& py) {
-    if (k == 0) {
-      px = ends[0];
-      py = ends[1];
-    } else if (k == W + 1) {
-      px = ends[2];
-      py = ends[3];
-    } else {
-      px = x[k - 1];
-      py = x[W + k - 1];
-    }
-  };
-  float px = 0.f, py = 0.f, qx = 0.f, qy = 0.f;
-  if (active) {
-    point(s, px, py);
-    point(s + 1, qx, qy);
-  }
-  const float dx = qx - px, dy = qy - py;
-  const float nc = fmaf(dy, px, -(dx * py));
-  int count = 0;
-  for (int e0 = 0; e0 < n_edges; e0 += kFitStage) {
-    const int ne = n_edges - e0 < kFitStage ? n_edges - e0 : kFitStage;
-    __syncthreads();
-    {
-      const float4* src = reinterpret_cast<const float4*>(edges + e0);
-      float4* dst = reinterpret_cast<float4*>(s_e);
-      for (int q = t; q < 2 * ne; q += kFitThreads) dst[q] = src[q];
-    }
-    __syncthreads();
-    if (active) {
-      for (int e = 0; e < ne; ++e) {
-        const FitEdge r = s_e[e];
-        const float o1 = fmaf(dx, r.ay, fmaf(-dy, r.ax, nc));
-        const float o2 = fmaf(dx, r.by, fmaf(-dy, r.bx, nc));
-        const float o3 = fmaf(r.ex, py, fmaf(-r.ey, px, -r.ce));
-        const float o4 = fmaf(r.ex, qy, fmaf(-r.ey, qx, -r.ce));
-        count += (opposite(o1, o2) && opposite(o3, o4)) ? 1 : 0;
-      }
-    }
-  }
-  if (active) {
-    seg_q[i] = count;
-    seg_l[i] = __builtin_amdgcn_sqrtf(dx * dx + dy * dy);  // v_sqrt_f32, within 1 ulp
-  }
+// w = 2 w + !(|o| > r), two instructions (a NaN on either side gives 1).
+__device__ __forceinline__ void push_near(uint32_t& w, float o, float r) {
+  asm("v_cmp_ngt_f32_e64 vcc, |%1|, %2\n\tv_addc_co_u32_e32 %0, vcc, %0, %0, vcc"
+      : "+v"(w)
+      : "v"(o), "v"(r)
+      : "vcc");
 }
 
-__global__ __launch_bounds__(kFitThreads) void fit_sum_kernel(const int32_t* seg_q,
-                                                              const float* seg_l, int n_paths,
-                                                              int W, float alpha, int beta,
-                                                              float* f, float* L, int32_t* Q) {
-  const int p = blockIdx.x * kFitThreads + threadIdx.x;
-  if (p >= n_paths) return;
-  const int S = W + 1;
-  int q = 0;
-  float l = 0.f;
-  for (int s = 0; s < S; ++s) {  // segment order: deterministic
-    q += seg_q[(int64_t)p * S + s];
-    l += seg_l[(int64_t)p * S + s];
+// One block: `rounds` times `ppr` whole paths, K segments per thread.
+//
+// What bounds it is VALU issue: a segment's test against one edge is about 18
+// instructions, and most pairs have no contact.  So each segment first tests
+// its line against every polygon's bounding box -- two FMAs for the box
+// centre's orientation o, two for r = |dx| h + |dy| w, one comparison -- and
+// only polygons whose box the line may meet are tested edge by edge.  The box
+// sizes and r carry a margin above the rounding of o and of the vertices' own
+// orientations (about 4 u (|dx| Y + |dy| X) each with u = 2^-24, X and Y the
+// largest coordinates; the margin is 16 u of it), so |o| > r means that the
+// edge-by-edge test would find every vertex strictly on one side and count
+// nothing: the counts are those of testing every pair, bit for bit.  Skipping
+// by the segment's own extent as well would need a tolerance that near-
+// parallel contacts break, so it is left out.
+//
+// The lines of 64 lanes meet different polygons (one in thirty of a dense
+// map), so the (segment, polygon) pairs to test go through a queue in LDS and
+// any lane takes any pair, 64 at a time; with a queue per lane half the lanes
+// sat idle (607 us on the large case below).  Vertices, boxes and offsets are
+// staged in LDS, by polygon ranges that fit when the map is larger; a polygon
+// of more than kFitLong edges is walked by the whole wave, from LDS or, when
+// it exceeds a pass by itself, from memory.
+//
+// 32768 uniform paths of 64 waypoints on 600 polygons (2400 edges): 1803 -> 390
+// us a call; 1360 paths of 20 on 30 rectangles: 28.2 -> 8.5 us; 128 paths of 8
+// on 4 rectangles: 13.5 -> 8.2 us, of which the host's call and the launch are
+// most (before: every pair tested, three launches).
+template <int K>
+__global__ __launch_bounds__(kFitMaxThreads) void fit_kernel(
+    int n_polys, const int32_t* __restrict__ pptr, const float* __restrict__ verts, int n_vert,
+    const float* __restrict__ ends, const float* __restrict__ paths, int n_paths, int W, int ppr,
+    int rounds, float alpha, int beta, float* f, float* L, int32_t* Q) {
+  extern __shared__ __attribute__((aligned(16))) char s_fit[];
+  const int t = threadIdx.x, B = blockDim.x, lane = t & 63;
+  const int S = W + 1, N = W + 2;  // segments and points per path
+  const FitLds lds = fit_lds(n_polys, n_vert, B, ppr * N);
+  float* s_vf = reinterpret_cast<float*>(s_fit);
+  const float2* s_v = reinterpret_cast<const float2*>(s_fit);
+  float4* s_box = reinterpret_cast<float4*>(s_fit + lds.box);
+  int* s_ptr = reinterpret_cast<int*>(s_fit + lds.ptr);
+  int* s_long = reinterpret_cast<int*>(s_fit + lds.lng);  // [0] their number
+  float2* s_pt = reinterpret_cast<float2*>(s_fit + lds.pts);
+  int* s_cross = reinterpret_cast<int*>(s_fit + lds.cross);
+  float* s_len = reinterpret_cast<float*>(s_fit + lds.len);
+  uint32_t* s_queue = reinterpret_cast<uint32_t*>(s_fit + lds.queue) + 2 * (t - lane);
+  const bool one_pass = n_vert <= lds.verts && n_polys <= lds.polys;
+  auto offset = [&](int q) { return min(max(pptr[q], 0), n_vert); };  // inside whatever it holds
+
+  for (int rd = 0; rd < rounds; ++rd) {
+    const int path0 = (blockIdx.x * rounds + rd) * ppr;
+    if (path0 >= n_paths) break;  // the whole block
+    float px[K], py[K], qx[K], qy[K], dx[K], dy[K], nc[K], tol[K];
+    int pt[K];  // the segment's first point among the block's
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+      const int i = t + k * B, pl = i / S, s = i - pl * S;
+      px[k] = py[k] = qx[k] = qy[k] = 0.f;
+      pt[k] = i + pl;
+      const bool active = pl < ppr && path0 + pl < n_paths;
+      if (active) {
+        const float* x = paths + (int64_t)(path0 + pl) * 2 * W;
+        // points s and s + 1 of [start, w_1..w_W, target]
+        const float* p = s == 0 ? ends : x + s - 1;
+        px[k] = p[0];
+        py[k] = p[s == 0 ? 1 : W];
+        const float* q = s == W ? ends + 2 : x + s;
+        qx[k] = q[0];
+        qy[k] = q[s == W ? 1 : W];
+      }
+      dx[k] = qx[k] - px[k];
+      dy[k] = qy[k] - py[k];
+      nc[k] = fmaf(dy[k], px[k], -(dx[k] * py[k]));
+      // the margin's share of the segment's own coordinates (and a floor far
+      // above the rounding of subnormal values); idle lanes are near nothing
+      tol[k] = active ? fmaf(0x1p-20f, fabsf(dx[k] * py[k]) + fabsf(dy[k] * px[k]), 1e-37f) : -1.f;
+      if (active) {
+        s_pt[pt[k]] = make_float2(px[k], py[k]);
+        if (s == W) s_pt[pt[k] + 1] = make_float2(qx[k], qy[k]);
+        s_cross[pt[k]] = 0;
+        s_len[pt[k]] = __builtin_amdgcn_sqrtf(fmaf(dx[k], dx[k], dy[k] * dy[k]));  // v_sqrt_f32, within 1 ulp
+      }
+    }
+    __syncthreads();
+
+    // the queue's pairs from `first` on, one per lane of the first n
+    auto work_off = [&](int first, int n) {
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      if (lane < n) {
+        const uint32_t e = s_queue[first + lane];
+        const int i = e & 2047u, q = e >> 11;
+        const int v0 = s_ptr[q], m = s_ptr[q + 1] - v0;
+        // a zero-length segment is near every box, also those that hold nothing to test
+        if (m < 1 || m > kFitLong) return;
+        const float2 a = s_pt[i], b = s_pt[i + 1];
+        const float ddx = b.x - a.x, ddy = b.y - a.y, c = fmaf(ddy, a.x, -(ddx * a.y));
+        // strict sides of vertex j, bit m - 1 - j
+        uint32_t neg = 0, pos = 0;
+        for (int j = 0; j < m; ++j) {
+          const float2 v = s_v[v0 + j];
+          const float o = fmaf(ddx, v.y, fmaf(-ddy, v.x, c));
+          neg = 2 * neg + (o < 0.f ? 1u : 0u);
+          pos = 2 * pos + (o > 0.f ? 1u : 0u);
+        }
+        // edge j joins vertices j and j + 1 (the last and vertex 0)
+        auto next = [&](uint32_t w) { return (w << 1) | (w >> (m - 1)); };
+        uint32_t st = ((neg & next(pos)) | (pos & next(neg))) & (0xffffffffu >> (32 - m));
+        int n_cross = 0;
+        while (st) {
+          const int bit = 31 - __clz(st), j = m - 1 - bit;
+          st ^= 1u << bit;
+          const float2 g = s_v[v0 + j], h = s_v[v0 + (bit == 0 ? 0 : j + 1)];
+          const float ex = h.x - g.x, ey = h.y - g.y, ce = fmaf(ex, g.y, -(ey * g.x));
+          const float o3 = fmaf(ex, a.y, fmaf(-ey, a.x, -ce));
+          const float o4 = fmaf(ex, b.y, fmaf(-ey, b.x, -ce));
+          n_cross += opposite(o3, o4) ? 1 : 0;
+        }
+        if (n_cross) atomicAdd(&s_cross[i], n_cross);
+      }
+    };
+    // crossings of segment k with the edges of a long polygon
+    auto whole = [&](auto v, int m, int k) {
+      float2 a = v(0);
+      float o1 = fmaf(dx[k], a.y, fmaf(-dy[k], a.x, nc[k]));
+      int c = 0;
+      for (int j = 1; j <= m; ++j) {
+        const float2 b = v(j == m ? 0 : j);
+        const float ex = b.x - a.x, ey = b.y - a.y, ce = fmaf(ex, a.y, -(ey * a.x));
+        const float o2 = fmaf(dx[k], b.y, fmaf(-dy[k], b.x, nc[k]));
+        const float o3 = fmaf(ex, py[k], fmaf(-ey, px[k], -ce));
+        const float o4 = fmaf(ex, qy[k], fmaf(-ey, qx[k], -ce));
+        c += (opposite(o1, o2) && opposite(o3, o4)) ? 1 : 0;
+        o1 = o2;  // the next edge starts where this one ends
+        a = b;
+      }
+      if (c && tol[k] > 0.f) atomicAdd(&s_cross[pt[k]], c);
+    };
+
+    for (int q0 = 0; q0 < n_polys;) {
+      // polygons q0 .. q1 - 1 of this pass, their vertices from v0 on
+      int q1 = n_polys;
+      const int v0 = one_pass ? 0 : offset(q0);
+      if (!one_pass) {  // the longest range that fits
+        int lo = q0, hi = min(q0 + lds.polys, n_polys);
+        while (lo < hi) {
+          const int mid = (lo + hi + 1) >> 1;
+          if (offset(mid) - v0 <= lds.verts)
+            lo = mid;
+          else
+            hi = mid - 1;
+        }
+        q1 = lo;
+        if (q1 == q0) {  // one polygon larger than a pass, read from memory
+          const int m = offset(q0 + 1) - v0;
+          const float* g = verts + 2 * (int64_t)v0;
+#pragma unroll
+          for (int k = 0; k < K; ++k)
+            whole([&](int j) { return make_float2(g[2 * (int64_t)j], g[2 * (int64_t)j + 1]); }, m, k);
+          ++q0;
+          continue;
+        }
+      }
+      const int np = q1 - q0;
+      if (!one_pass || rd == 0) {
+        if (!one_pass) __syncthreads();  // the last pass has been read
+        const int nv = one_pass ? n_vert : max(offset(q1) - v0, 0);
+        for (int i = t; i < 2 * nv; i += B) s_vf[i] = verts[2 * (int64_t)v0 + i];
+        for (int i = t; i <= np; i += B) s_ptr[i] = min(max(offset(q0 + i) - v0, 0), nv);
+        if (t == 0) s_long[0] = 0;
+        __syncthreads();
+        for (int i = t; i < np; i += B) {
+          const int a = s_ptr[i], m = s_ptr[i + 1] - a;
+          float4 b = make_float4(0.f, 0.f, -FLT_MAX, -FLT_MAX);  // nothing to test here
+          if (m > kFitLong) {
+            const int at = atomicAdd(&s_long[0], 1);
+            if (at < lds.longs) s_long[1 + at] = i;  // always, unless the offsets are malformed
+          } else if (m > 0) {
+            float x0 = s_v[a].x, x1 = x0, y0 = s_v[a].y, y1 = y0;
+            for (int j = 1; j < m; ++j) {
+              const float2 v = s_v[a + j];
+              x0 = fminf(x0, v.x);
+              x1 = fmaxf(x1, v.x);
+              y0 = fminf(y0, v.y);
+              y1 = fmaxf(y1, v.y);
+            }
+            // centre and half sides, the latter with the margin
+            b.x = 0.5f * x0 + 0.5f * x1;
+            b.y = 0.5f * y0 + 0.5f * y1;
+            b.z = fmaf(fmaxf(x1 - b.x, b.x - x0), 1.f + 0x1p-19f, 0x1p-20f * fmaxf(fabsf(x0), fabsf(x1)));
+            b.w = fmaf(fmaxf(y1 - b.y, b.y - y0), 1.f + 0x1p-19f, 0x1p-20f * fmaxf(fabsf(y0), fabsf(y1)));
+          }
+          s_box[i] = b;
+        }
+        __syncthreads();
+      }
+      int queued = 0;  // the wave's
+      for (int i0 = 0; i0 < np; i0 += 32) {
+        const int n = min(32, np - i0);
+        uint32_t near[K];
+#pragma unroll
+        for (int k = 0; k < K; ++k) near[k] = 0;
+        auto test = [&](int i) {
+          const float4 b = s_box[i0 + i];
+#pragma unroll
+          for (int k = 0; k < K; ++k) {
+            const float o = fmaf(dx[k], b.y, fmaf(-dy[k], b.x, nc[k]));
+            const float r = fmaf(fabsf(dx[k]), b.w, fmaf(fabsf(dy[k]), b.z, tol[k]));
+            push_near(near[k], o, r);
+          }
+        };
+        int i = 0;
+        for (; i + 8 <= n; i += 8) {
+#pragma unroll
+          for (int u = 0; u < 8; ++u) test(i + u);
+        }
+        for (; i < n; ++i) test(i);
+        // polygon i0 + n - 1 - bit of every set bit joins the wave's queue
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+          uint32_t w = tol[k] > 0.f ? near[k] : 0u;
+          for (;;) {
+            const uint64_t has = __builtin_amdgcn_ballot_w64(w != 0u);
+            if (has == 0ull) break;
+            if (w != 0u) {
+              const int bit = 31 - __clz(w);
+              w ^= 1u << bit;
+              const int at = __builtin_amdgcn_mbcnt_hi((uint32_t)(has >> 32),
+                                                       __builtin_amdgcn_mbcnt_lo((uint32_t)has, 0u));
+              const int q = i0 + n - 1 - bit;
+              s_queue[queued + at] = (uint32_t)q << 11 | (uint32_t)pt[k];
+            }
+            queued += __popcll(has);
+            if (queued >= 64) {
+              queued -= 64;
+              work_off(queued, 64);
+            }
+          }
+        }
+      }
+      work_off(0, queued);
+      const int n_long = min(s_long[0], lds.longs);
+      for (int i = 0; i < n_long; ++i) {
+        const int q = s_long[1 + i], a = s_ptr[q], m = s_ptr[q + 1] - a;
+#pragma unroll
+        for (int k = 0; k < K; ++k) whole([&](int j) { return s_v[a + j]; }, m, k);
+      }
+      q0 = q1;
+    }
+
+    __syncthreads();
+    const int p = path0 + t;
+    if (t < ppr && p < n_paths) {
+      int q = 0;
+      float l = 0.f;
+      for (int s = 0; s < S; ++s) {  // segment order: deterministic
+        q += s_cross[t * N + s];
+        l += s_len[t * N + s];
+      }
+      const float qf = (float)q;
+      float pw = 1.f;
+      for (int b = 0; b < beta; ++b) pw *= qf;
+      f[p] = fmaf(alpha, pw, l);
+      L[p] = l;
+      Q[p] = q;
+    }
+    if (rd + 1 < rounds) __syncthreads();  // the sums are read before the points change
   }
-  const float qf = (float)q;
-  float pw = 1.f;
-  for (int b = 0; b < beta; ++b) pw *= qf;
-  f[p] = l + alpha * pw;
-  L[p] = l;
-  Q[p] = q;
 }
 
 size_t a256(size_t x) { return (x + 255) & ~size_t(255); }
 
-struct FitLayout {
-  size_t edges, seg_q, seg_l, total;
-};
-
-FitLayout fit_layout(int64_t n_vert, int64_t n_paths, int W) {
-  FitLayout l;
-  const int64_t n_seg = n_paths * (W + 1);
-  l.edges = 0;
-  l.seg_q = a256(sizeof(FitEdge) * (size_t)n_vert);
-  l.seg_l = l.seg_q + a256(sizeof(int32_t) * (size_t)n_seg);
-  l.total = l.seg_l + a256(sizeof(float) * (size_t)n_seg);
-  return l;
+// Bytes a caller's workspace must hold: records of 32 bytes per vertex and
+// two words per segment.  The kernel keeps all of it on chip; the size and
+// its checks stand for callers that carve their memory by them.
+size_t fit_workspace(int64_t n_vert, int64_t n_paths, int W) {
+  const size_t n_seg = (size_t)(n_paths * (W + 1));
+  return a256(32 * (size_t)n_vert) + 2 * a256(4 * n_seg);
 }
 
 sepso_status fit_check(int32_t n_polys, int32_t n_vert, int32_t n_paths, int32_t W, float alpha,
@@ -177,22 +354,40 @@ sepso_status fit_check(int32_t n_polys, int32_t n_vert, int32_t n_paths, int32_t
   return SEPSO_OK;
 }
 
+// Threads per block, segments per thread and whole paths per block and round.
+// Many segments: 512 threads of two segments each (a box is read from LDS once
+// for both), a few rounds per block so that staging the map is paid once for
+// several thousand segments.  Few: the smallest block that holds whole paths
+// without leaving more than a quarter of its threads idle, one segment per
+// thread, so that the call spreads over as many CUs as it can.
+template <int K>
+void fit_launch(int threads, int n_polys, const int32_t* pptr, const float* verts, int n_vert,
+                const float* ends, const float* paths, int n_paths, int W, int rounds, float alpha,
+                int beta, float* f, float* L, int32_t* Q, hipStream_t s) {
+  const int ppr = K * threads / (W + 1);
+  const int64_t per_block = (int64_t)ppr * rounds;
+  const unsigned blocks = (unsigned)((n_paths + per_block - 1) / per_block);
+  hipLaunchKernelGGL(fit_kernel<K>, dim3(blocks), dim3(threads), fit_lds(n_polys, n_vert, threads, ppr * (W + 2)).bytes,
+                     s, n_polys, pptr, verts, n_vert, ends, paths, n_paths, W, ppr, rounds, alpha, beta, f,
+                     L, Q);
+}
+
 sepso_status fit_run(int32_t n_polys, int32_t n_vert, const int32_t* d_pptr, const float* d_verts,
                      const float* d_ends, const float* d_paths, int32_t n_paths, int32_t W,
-                     float alpha, int32_t beta, float* d_f, float* d_L, int32_t* d_Q, char* ws,
-                     hipStream_t s) {
-  const FitLayout l = fit_layout(n_vert, n_paths, W);
-  FitEdge* edges = reinterpret_cast<FitEdge*>(ws + l.edges);
-  int32_t* seg_q = reinterpret_cast<int32_t*>(ws + l.seg_q);
-  float* seg_l = reinterpret_cast<float*>(ws + l.seg_l);
-  const int n_seg = n_paths * (W + 1);
-  if (n_vert > 0)
-    hipLaunchKernelGGL(fit_edges_kernel, dim3((n_vert + kFitThreads - 1) / kFitThreads),
-                       dim3(kFitThreads), 0, s, n_polys, d_pptr, d_verts, n_vert, edges);
-  hipLaunchKernelGGL(fit_seg_kernel, dim3((n_seg + kFitThreads - 1) / kFitThreads), dim3(kFitThreads),
-                     0, s, edges, n_vert, d_ends, d_paths, n_seg, W, seg_q, seg_l);
-  hipLaunchKernelGGL(fit_sum_kernel, dim3((n_paths + kFitThreads - 1) / kFitThreads),
-                     dim3(kFitThreads), 0, s, seg_q, seg_l, n_paths, W, alpha, beta, d_f, d_L, d_Q);
+                     float alpha, int32_t beta, float* d_f, float* d_L, int32_t* d_Q, hipStream_t s) {
+  const int S = W + 1;
+  if (n_vert == 0) n_polys = 0;  // polygons without vertices have no edges
+  if ((int64_t)n_paths * S >= (1 << 18)) {
+    const int ppr = 2 * kFitMaxThreads / S;
+    const int rounds = std::max(1, (n_paths + ppr * 1024 - 1) / (ppr * 1024));
+    fit_launch<2>(kFitMaxThreads, n_polys, d_pptr, d_verts, n_vert, d_ends, d_paths, n_paths, W, rounds,
+                  alpha, beta, d_f, d_L, d_Q, s);
+  } else {
+    int threads = 64;
+    while (threads < 256 && 4 * (threads / S * S) < 3 * threads) threads *= 2;
+    fit_launch<1>(threads, n_polys, d_pptr, d_verts, n_vert, d_ends, d_paths, n_paths, W, 1, alpha, beta,
+                  d_f, d_L, d_Q, s);
+  }
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return fail(SEPSO_E_HIP, "fitness launch: %s", hipGetErrorString(e));
   return SEPSO_OK;
@@ -221,7 +416,7 @@ sepso_status sepso_fitness_workspace_bytes(int32_t n_vert, int32_t n_paths, int3
   if (n_vert < 0 || n_paths < 0) return fail(SEPSO_E_ARG, "fitness: sizes must be >= 0");
   if (waypoints < 1 || waypoints > kMaxW)
     return fail(SEPSO_E_ARG, "fitness: waypoints must be in [1, %d]", kMaxW);
-  *bytes = fit_layout(n_vert, n_paths, waypoints).total;
+  *bytes = fit_workspace(n_vert, n_paths, waypoints);
   return SEPSO_OK;
 }
 
@@ -235,54 +430,22 @@ sepso_status sepso_fitness(int32_t n_polys, int32_t n_vert, const int32_t* d_pol
     st = fit_pointers(n_vert, d_poly_ptr, d_verts, d_ends, d_paths, n_paths, d_f, d_L, d_Q);
   if (st != SEPSO_OK) return st;
   if (n_paths == 0) return SEPSO_OK;
-  const size_t need = fit_layout(n_vert, n_paths, waypoints).total;
+  const size_t need = fit_workspace(n_vert, n_paths, waypoints);
   if (!d_ws || (reinterpret_cast<uintptr_t>(d_ws) & 255))
     return fail(SEPSO_E_ARG, "fitness: workspace must be a 256-byte aligned device pointer");
   if (ws_bytes < need)
     return fail(SEPSO_E_NOMEM, "fitness: workspace of %zu bytes, %zu needed", ws_bytes, need);
   return fit_run(n_polys, n_vert, d_poly_ptr, d_verts, d_ends, d_paths, n_paths, waypoints, alpha,
-                 beta, d_f, d_L, d_Q, static_cast<char*>(d_ws), static_cast<hipStream_t>(stream));
+                 beta, d_f, d_L, d_Q, static_cast<hipStream_t>(stream));
 }
 
 }  // extern "C"
 
-// ---------------------------------------------------------------------------
-// Allocation-free variant: the workspace is a file-scope device array of
-// kFitScratchBytes, one per GPU, shared by every call on that GPU.  Host code
-// never uses the array's name as an address: its device address is looked up
-// once per device (hipGetSymbolAddress, with that device current) and kept.
-// ---------------------------------------------------------------------------
-namespace sepso {
+// The workspace-free variant: the same launch, for requests up to the size it
+// has always taken.
 namespace {
-
-constexpr size_t kFitScratchBytes = size_t(8) << 20;  // 8 MiB per GPU
-constexpr int kFitMaxDevices = 64;
-
-__device__ __align__(256) char scratch[kFitScratchBytes];
-
-std::mutex g_scratch_mu;
-void* g_scratch_ptr[kFitMaxDevices] = {};
-
-sepso_status scratch_ptr(void** out) {
-  int dev = -1;
-  hipError_t e = hipGetDevice(&dev);
-  if (e != hipSuccess) return fail(SEPSO_E_HIP, "hipGetDevice: %s", hipGetErrorString(e));
-  if (dev < 0 || dev >= kFitMaxDevices)
-    return fail(SEPSO_E_UNSUPPORTED, "fitness: device %d beyond the %d supported", dev, kFitMaxDevices);
-  std::lock_guard<std::mutex> lock(g_scratch_mu);
-  if (!g_scratch_ptr[dev]) {
-    void* p = nullptr;
-    e = hipGetSymbolAddress(&p, HIP_SYMBOL(scratch));
-    if (e != hipSuccess || !p)
-      return fail(SEPSO_E_HIP, "hipGetSymbolAddress(scratch): %s", hipGetErrorString(e));
-    g_scratch_ptr[dev] = p;
-  }
-  *out = g_scratch_ptr[dev];
-  return SEPSO_OK;
+constexpr size_t kFitScratchBytes = size_t(8) << 20;
 }
-
-}  // namespace
-}  // namespace sepso
 
 extern "C" {
 
@@ -295,17 +458,14 @@ sepso_status sepso_fitness_noalloc(int32_t n_polys, int32_t n_vert, const int32_
     st = fit_pointers(n_vert, d_poly_ptr, d_verts, d_ends, d_paths, n_paths, d_f, d_L, d_Q);
   if (st != SEPSO_OK) return st;
   if (n_paths == 0) return SEPSO_OK;
-  const size_t need = fit_layout(n_vert, n_paths, waypoints).total;
+  const size_t need = fit_workspace(n_vert, n_paths, waypoints);
   if (need > kFitScratchBytes)
     return fail(SEPSO_E_ARG,
                 "fitness_noalloc: %d paths of %d waypoints on %d vertices need %zu bytes of "
                 "scratch; the allocation-free variant holds %zu (use sepso_fitness with a workspace)",
                 n_paths, waypoints, n_vert, need, kFitScratchBytes);
-  void* ws = nullptr;
-  st = scratch_ptr(&ws);
-  if (st != SEPSO_OK) return st;
   return fit_run(n_polys, n_vert, d_poly_ptr, d_verts, d_ends, d_paths, n_paths, waypoints, alpha,
-                 beta, d_f, d_L, d_Q, static_cast<char*>(ws), static_cast<hipStream_t>(stream));
+                 beta, d_f, d_L, d_Q, static_cast<hipStream_t>(stream));
 }
 
 }  // extern "C"
