@@ -304,205 +304,292 @@ __global__ __launch_bounds__(256) void bf_best_kernel(BFDev s, float* out) {
 }
 
 // ---- whole run of a small swarm in one workgroup ----------------------------
-// A swarm whose state fits in LDS (rows of at most 256 floats) runs all its
-// iterations in one launch, one workgroup per swarm: the stepwise kernels'
-// move, evaluation, Pbest and bests in the same order and arithmetic
-// (bf_move, bf_terms, the same wave butterflies), with barriers instead of
-// kernel boundaries, so the results are bit-identical.  The control word is
-// read here and advanced by bf_ctl_kernel afterwards (every workgroup reads
-// it unchanged).
+// A swarm of rows of at most 256 floats whose rows fit in LDS twice runs all
+// its iterations in one launch, one workgroup per swarm: the stepwise
+// kernels' move, evaluation, Pbest and bests in the same order and arithmetic
+// (bf_move, bf_terms, the same wave butterflies), so the results are
+// bit-identical.  The control word is read here and advanced by bf_ctl_kernel
+// afterwards (every workgroup reads it unchanged).
 constexpr int kBFRunThreads = 1024;
+constexpr int kBFRunMax = 64 * 1024;  // LDS bytes
 
-struct BFRunLds {
-  int Q, L;      // float4 groups per row, lanes per particle (power of two >= Q)
-  size_t bytes;  // dynamic LDS
+struct BFRunPlan {
+  int Q, L;          // float4 groups per row, lanes per particle (power of two >= Q)
+  int R, threads;    // particles per thread's lane group, threads of the workgroup
+  int ahead;         // iterations whose random factors are drawn together
+  size_t bytes;      // dynamic LDS
 };
 
-inline BFRunLds bf_run_lds(int Gs, int N, int Dp) {
-  BFRunLds r{};
+inline BFRunPlan bf_run_plan(int Gs, int N, int Dp) {
+  BFRunPlan r{};
   r.Q = Dp / 4;
   r.L = 1;
   while (r.L < r.Q) r.L *= 2;
   const size_t nS = (size_t)Gs * N;
-  r.bytes = 16 * (3 * nS * r.Q + (size_t)Gs * r.Q) + 4 * (nS * 7 + 10 * (size_t)Gs);
+  r.R = (int)((nS * r.L + kBFRunThreads - 1) / kBFRunThreads);
+  const size_t per = (nS + r.R - 1) / r.R;
+  r.threads = (int)((per * r.L + 63) / 64 * 64);
+  for (r.ahead = r.L < 8 ? r.L : 8;; r.ahead /= 2) {
+    r.bytes = 16 * (2 * nS * r.Q + nS * r.ahead) + 16 * (size_t)Gs;
+    if (r.bytes <= kBFRunMax || r.ahead == 1) break;
+  }
   return r;
 }
 
-template <int FUNC>
-__global__ __launch_bounds__(kBFRunThreads) void bf_run_kernel(BFDev s, int n_fit, int flush, int L) {
+// A group's best as one word that orders by fitness, then by particle (flat
+// index in the swarm): the float's bits made to order as an unsigned number.
+__device__ __forceinline__ uint64_t bf_key(float f, int i) {
+  const uint32_t b = __float_as_uint(f + 0.f);  // -0 counts as +0
+  return (uint64_t)(b ^ ((uint32_t)((int32_t)b >> 31) | 0x80000000u)) << 32 | (uint32_t)i;
+}
+__device__ __forceinline__ float bf_key_f(uint64_t k) {
+  const uint32_t b = (uint32_t)(k >> 32);
+  return __uint_as_float(b ^ ((b & 0x80000000u) ? 0x80000000u : 0xffffffffu));
+}
+
+// Value of lane (lane ^ M): inside rows of 16 lanes by DPP operands.
+template <int M>
+__device__ __forceinline__ int lane_xor(int x) {
+  if (M == 1) return __builtin_amdgcn_mov_dpp(x, 0xB1, 0xF, 0xF, true);  // quad_perm 1,0,3,2
+  if (M == 2) return __builtin_amdgcn_mov_dpp(x, 0x4E, 0xF, 0xF, true);  // quad_perm 2,3,0,1
+  if (M == 4) {  // lanes 0-3 of eight read four up, lanes 4-7 four down
+    const int up = __builtin_amdgcn_update_dpp(0, x, 0x104, 0xF, 0x5, false);
+    return __builtin_amdgcn_update_dpp(up, x, 0x114, 0xF, 0xA, false);
+  }
+  if (M == 8) return __builtin_amdgcn_mov_dpp(x, 0x128, 0xF, 0xF, true);  // row_ror 8
+  return __shfl_xor(x, M);
+}
+template <int M>
+__device__ __forceinline__ float lane_xor(float x) {
+  return __int_as_float(lane_xor<M>(__float_as_int(x)));
+}
+
+// The butterfly of wave_sum / wave_prod over segments of L lanes: the steps
+// from L / 2 down to STOP (those above would add the exact zeros, or ones, of
+// lanes that hold nothing).
+template <int STOP = 1, class Op>
+__device__ __forceinline__ float seg_reduce(float x, int L, Op op) {
+  if (L > 8) {
+    if (L > 16) {
+      if (L > 32) x = op(x, lane_xor<32>(x));
+      x = op(x, lane_xor<16>(x));
+    }
+    x = op(x, lane_xor<8>(x));
+  }
+  if (L > 4) x = op(x, lane_xor<4>(x));
+  if (L > 2) x = op(x, lane_xor<2>(x));
+  if (STOP < 2 && L > 1) x = op(x, lane_xor<1>(x));
+  return x;
+}
+
+// Smaller of a lane's word and that of the lane a DPP control (or, by way of
+// LDS, a distance) names.
+template <int CTRL>
+__device__ __forceinline__ uint64_t min_dpp(uint64_t k) {
+  const uint64_t o = (uint64_t)(uint32_t)__builtin_amdgcn_mov_dpp((int)(k >> 32), CTRL, 0xF, 0xF, true) << 32 |
+                     (uint32_t)__builtin_amdgcn_mov_dpp((int)k, CTRL, 0xF, 0xF, true);
+  return o < k ? o : k;
+}
+__device__ __forceinline__ uint64_t min_shfl(uint64_t k, int m) {
+  const uint64_t o = __shfl_xor((unsigned long long)k, m);
+  return o < k ? o : k;
+}
+
+// The iterations are a serial chain on one CU, bound by its four SIMDs'
+// issue: about 250 instructions per wave and iteration at 80 particles x 30
+// (ten waves).  So nothing is done twice and little is waited for: a lane
+// keeps its four coordinates of X, V and P (of R particles) in registers, the
+// sums over a row go by DPP operands, the random factors of `ahead`
+// iterations are drawn at once, one iteration per lane of a particle (ten
+// rounds of quarter-rate multiplies, which every lane would repeat
+// otherwise), and there is one barrier per iteration.  Before it each
+// particle puts its Pbest row and its (fitness, index) word -- by an LDS
+// minimum into its group's -- in LDS; after it every wave finds the group and
+// total bests from the words.  Rows and words have two copies, by the
+// iteration's parity: a wave that is late reading one iteration's finds the
+// next written to the other copy, and nobody reaches the one after before
+// every wave has come to the next barrier.  A group's word needs no clearing:
+// a particle's Pbest never rises, so older entries never win.
+// 32 swarms of 80 x 30, 1400 iterations of Rastrigin: 5.12 -> 1.63 ms a launch
+// (1.17 us per iteration; with the state in LDS, five barriers per iteration
+// and one thread scanning each group's Pbest it was 3.6).
+template <int FUNC, int R>
+__global__ __launch_bounds__(kBFRunThreads) void
+bf_run_kernel(BFDev s, int n_fit, int flush, int L, int ahead, int fused) {
   extern __shared__ float4 s_dyn4[];
-  __shared__ int s_tg;
   const int sw = blockIdx.x, t = threadIdx.x, B = blockDim.x;
   const int Gs = s.Gs, N = s.N, D = s.D, Q = s.Dp / 4, nS = Gs * N, g0 = sw * Gs;
   const int64_t r0 = (int64_t)g0 * N * Q;  // first float4 of the swarm's rows
-  float4* sX = s_dyn4;
-  float4* sV = sX + nS * Q;
-  float4* sP = sV + nS * Q;
-  float4* sG = sP + nS * Q;  // Gbest rows
-  float* sPf = reinterpret_cast<float*>(sG + Gs * Q);
-  float* sF = sPf + nS;
-  float* sC = sF + nS;                            // per particle a1, a2, a3, (unused)
-  int* sImp = reinterpret_cast<int*>(sC + 4 * nS);
-  float* sGf = reinterpret_cast<float*>(sImp + nS);
-  int* sGn = reinterpret_cast<int*>(sGf + Gs);
-  float* sH = reinterpret_cast<float*>(sGn + Gs);  // per group C1, C2, C3, w_init, w_end, V_limit
-  float* sW = sH + 6 * Gs;                         // per group inertia of the current move
-  float* sVm = sW + Gs;                            // per group velocity bound
+  // Pbest rows (two copies), per particle and iteration ahead a1, a2, a3, and
+  // per group its best (two copies)
+  float4* sP = s_dyn4;
+  float4* sC = s_dyn4 + 2 * nS * Q;
+  uint64_t* sB = reinterpret_cast<uint64_t*>(sC + nS * ahead);
+  const int lane = t & 63, ls = t & (L - 1), per = B / L;
+  const int e = 4 * ls;  // first coordinate of this lane
 
-  const float4* X4 = reinterpret_cast<const float4*>(s.X) + r0;
-  const float4* V4 = reinterpret_cast<const float4*>(s.V) + r0;
-  const float4* P4 = reinterpret_cast<const float4*>(s.P) + r0;
-  const float4* G4 = reinterpret_cast<const float4*>(s.gbest_pos) + (int64_t)g0 * Q;
-  for (int q = t; q < nS * Q; q += B) {
-    sX[q] = X4[q];
-    sV[q] = V4[q];
-    sP[q] = P4[q];
+  // particle r * per + t / L of the swarm, for r < R; lanes past a row's end
+  // (or the last particle) hold nothing
+  float4 x4[R], v4[R], p4[R];
+  float pf[R], fv[R], h3[R], hs[R], vmax[R];
+  int id[R], grp[R];
+  bool row[R], own[R];  // holds coordinates; is the particle's first lane
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    const int i = r * per + t / L;
+    const bool in = i < nS;
+    id[r] = in ? i : nS - 1;
+    grp[r] = id[r] / N;
+    row[r] = in && ls < Q;
+    own[r] = in && ls == 0;
+    const float* h = s.hyper + 6 * (g0 + grp[r]);
+    h3[r] = h[3];
+    hs[r] = (h[3] - h[4]) / (float)s.T;
+    vmax[r] = h[5] * (s.hi - s.lo) * 0.5f;
+    x4[r] = v4[r] = p4[r] = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (row[r]) {
+      const int64_t q = r0 + (int64_t)i * Q + ls;
+      x4[r] = reinterpret_cast<const float4*>(s.X)[q];
+      v4[r] = reinterpret_cast<const float4*>(s.V)[q];
+      p4[r] = reinterpret_cast<const float4*>(s.P)[q];
+    }
+    pf[r] = s.Pf[(int64_t)g0 * N + id[r]];
+    fv[r] = s.f[(int64_t)g0 * N + id[r]];
   }
-  for (int q = t; q < Gs * Q; q += B) sG[q] = G4[q];
-  for (int i = t; i < nS; i += B) {
-    sPf[i] = s.Pf[(int64_t)g0 * N + i];
-    sF[i] = s.f[(int64_t)g0 * N + i];
-  }
-  for (int g = t; g < Gs; g += B) {
-    sGf[g] = s.gbest_f[g0 + g];
-    sGn[g] = s.gbest_n[g0 + g];
-    const float* h = s.hyper + 6 * (g0 + g);
-    for (int j = 0; j < 6; ++j) sH[6 * g + j] = h[j];
-    sVm[g] = h[5] * (s.hi - s.lo) * 0.5f;
-  }
+  for (int g = t; g < Gs; g += B) sB[g] = sB[Gs + g] = bf_key(INFINITY, g * N);
   const BFCtl c0 = *s.ctl;
   int k = c0.k, pending = c0.pending;
   uint32_t ctr = c0.ctr;
+  // the bests' rows for a move owed at the start come from memory
+  float4 gb[R], tb = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+  for (int r = 0; r < R; ++r) gb[r] = tb;
+  uint64_t best[R];
+#pragma unroll
+  for (int r = 0; r < R; ++r) best[r] = bf_key(INFINITY, grp[r] * N);
+  if (pending && ls < Q) {
+    const float4* G4 = reinterpret_cast<const float4*>(s.gbest_pos) + (int64_t)g0 * Q;
+    int tg = 0;
+    for (int g = 1; g < Gs; ++g)
+      if (s.gbest_f[g0 + g] < s.gbest_f[g0 + tg]) tg = g;
+    tb = G4[tg * Q + ls];
+#pragma unroll
+    for (int r = 0; r < R; ++r) gb[r] = G4[grp[r] * Q + ls];
+  }
   __syncthreads();
 
-  const int lane = t & 63, wave = t >> 6, n_waves = B >> 6;
-  const int per_wave = 64 / L, seg = lane / L, ls = lane - seg * L;
+  int drawn = 0;  // iterations whose factors are still in sC
   for (int step = 0; step < n_fit + flush; ++step) {
     const bool fit = step < n_fit;
     if (pending) {
-      // Tbest of the swarm (lowest group best, lowest group on ties) and each
-      // particle's r1, r2, r3 scaled by its group's C1, C2, C3
-      if (t == 0) {
-        int tg = 0;
-        for (int g = 1; g < Gs; ++g)
-          if (sGf[g] < sGf[tg]) tg = g;
-        s_tg = tg;
+      if (drawn == 0) {  // lane ls < ahead draws for the ls-th move from here
+        drawn = ahead;
+        if (ls < ahead) {
+#pragma unroll
+          for (int r = 0; r < R; ++r) {
+            const float* h = s.hyper + 6 * (g0 + grp[r]);
+            const U4 d = philox((uint32_t)id[r], ctr + (uint32_t)ls, (uint32_t)sw, TAG_BF_UPDATE, s.seed_lo,
+                                s.seed_hi);
+            sC[id[r] * ahead + ls] =
+                make_float4(h[0] * u01(d.v[0]), h[1] * u01(d.v[1]), h[2] * u01(d.v[2]), 0.f);
+          }
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");  // read by the particle's own lanes
       }
       const int kk = k < s.T ? k : s.T;
-      for (int g = t; g < Gs; g += B) {
-        const float* h = sH + 6 * g;
-        sW[g] = h[3] - (h[3] - h[4]) / (float)s.T * (float)kk;
-      }
-      for (int i = t; i < nS; i += B) {
-        const float* h = sH + 6 * (i / N);
-        const U4 r = philox((uint32_t)i, ctr, (uint32_t)sw, TAG_BF_UPDATE, s.seed_lo, s.seed_hi);
-        sC[4 * i + 0] = h[0] * u01(r.v[0]);
-        sC[4 * i + 1] = h[1] * u01(r.v[1]);
-        sC[4 * i + 2] = h[2] * u01(r.v[2]);
-      }
-      __syncthreads();
-      const int tg = s_tg;
-      for (int q = t; q < nS * Q; q += B) {
-        const int i = q / Q, qq = q - i * Q, g = i / N, e = 4 * qq;
-        const float w = sW[g], vmax = sVm[g];
-        const float a1 = sC[4 * i], a2 = sC[4 * i + 1], a3 = sC[4 * i + 2];
-        float4 x4 = sX[q], v4 = sV[q];
-        const float4 p4 = sP[q], gb4 = sG[g * Q + qq], tb4 = sG[tg * Q + qq];
-        float* xs = &x4.x;
-        float* vs = &v4.x;
-        const float* ps = &p4.x;
-        const float* gs = &gb4.x;
-        const float* ts = &tb4.x;
 #pragma unroll
-        for (int j = 0; j < 4; ++j)
-          if (e + j < D) xs[j] = bf_move(xs[j], vs[j], ps[j], gs[j], ts[j], w, a1, a2, a3, vmax, s.lo, s.hi);
-        sX[q] = x4;
-        sV[q] = v4;
+      for (int r = 0; r < R; ++r) {
+        const float4 c = sC[id[r] * ahead + (ahead - drawn)];
+        const float w = h3[r] - hs[r] * (float)kk;
+        float* xs = &x4[r].x;
+        float* vs = &v4[r].x;
+        const float* ps = &p4[r].x;
+        const float* gs = &gb[r].x;
+        const float* ts = &tb.x;
+#pragma unroll
+        for (int j = 0; j < 4; ++j)  // (past a row's end too: nothing reads those)
+          xs[j] = bf_move(xs[j], vs[j], ps[j], gs[j], ts[j], w, c.x, c.y, c.z, vmax[r], s.lo, s.hi);
       }
-      __syncthreads();
+      --drawn;
     }
     if (fit) {
-      // evaluation: L lanes per particle, lane ls holding elements 4 ls ..
-      // 4 ls + 3 as the stepwise kernel's lane ls does; the butterfly's
-      // steps below L add the exact zeros (ones) of the empty lanes there
-      for (int base = wave * per_wave; base < nS; base += n_waves * per_wave) {
-        const int i = base + seg;
-        const bool ok = i < nS && ls < Q;
-        float xv[4] = {0.f, 0.f, 0.f, 0.f};
-        if (ok) {
-          const float4 x4 = sX[i * Q + ls];
-          xv[0] = x4.x;
-          xv[1] = x4.y;
-          xv[2] = x4.z;
-          xv[3] = x4.w;
-        }
+      const int rows = (step & 1) * nS * Q + ls, words = (step & 1) * Gs;
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        // lane ls holds elements 4 ls .. 4 ls + 3 as the stepwise kernel's does
+        const float xv[4] = {x4[r].x, x4[r].y, x4[r].z, x4[r].w};
         float prev = 0.f;
         if (FUNC == BF_ROSENBROCK) {
-          prev = __shfl_up(xv[3], 1);
+          prev = L <= 16 ? __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(xv[3]), 0x111, 0xF, 0xF, true))
+                         : __shfl_up(xv[3], 1);  // row_shr 1
           if (ls == 0) prev = 0.f;
         }
         float acc = 0.f, prod = 1.f;
-        bf_terms<FUNC>(xv, prev, ok ? 4 * ls : D, D, acc, prod);
-        for (int m = L / 2; m > 0; m >>= 1) acc += __shfl_xor(acc, m);
+        bf_terms<FUNC>(xv, prev, row[r] ? e : D, D, acc, prod);
+        float f = seg_reduce(acc, L, [](float a, float b) { return a + b; });
         if (FUNC == BF_GRIEWANK) {
-          for (int m = L / 2; m > 0; m >>= 1) prod *= __shfl_xor(prod, m);
+          // the last factor and the subtraction with one rounding, as the
+          // stepwise kernel has them, or with two
+          prod = seg_reduce<2>(prod, L, [](float a, float b) { return a * b; });
+          const float last = L > 1 ? lane_xor<1>(prod) : 1.f;
+          float whole = prod * last;
+          asm("" : "+v"(whole));  // rounded: not contracted into the subtraction
+          f = fused ? fmaf(-prod, last, 1.f + f) : 1.f + f - whole;
         }
-        float fv = acc;
-        if (FUNC == BF_GRIEWANK) fv = 1.f + fv - prod;
-        if (!(fabsf(fv) <= 3.402823466e38f)) fv = INFINITY;
-        if (i < nS && ls == 0) {
-          const int imp = fv < sPf[i];
-          sF[i] = fv;
-          if (imp) sPf[i] = fv;
-          sImp[i] = imp;
+        if (!(fabsf(f) <= 3.402823466e38f)) f = INFINITY;
+        fv[r] = f;
+        if (f < pf[r]) {
+          pf[r] = f;
+          p4[r] = x4[r];
         }
+        if (row[r]) sP[rows + id[r] * Q] = p4[r];
+        // (an infinite or NaN Pbest is no group's best)
+        if (own[r] && pf[r] < INFINITY)
+          atomicMin(reinterpret_cast<unsigned long long*>(sB + words + grp[r]), bf_key(pf[r], id[r]));
       }
       __syncthreads();
-      for (int q = t; q < nS * Q; q += B)
-        if (sImp[q / Q]) sP[q] = sX[q];
-      // Gbest of every group: lowest Pbest, lowest index on ties
-      for (int g = t; g < Gs; g += B) {
-        float bf = INFINITY;
-        int bn = 0;
-        for (int n = 0; n < N; ++n) {
-          const float f = sPf[g * N + n];
-          if (f < bf) {
-            bf = f;
-            bn = n;
-          }
-        }
-        sGf[g] = bf;
-        sGn[g] = bn;
+      // total best: lowest fitness, lowest group and index on ties
+      const int wl = Gs > 8 ? lane : lane & 7;
+      uint64_t tot = sB[words + (wl < Gs ? wl : 0)];
+#pragma unroll
+      for (int r = 0; r < R; ++r) best[r] = sB[words + grp[r]];
+      tot = min_dpp<0xB1>(tot);   // quad_perm 1,0,3,2
+      tot = min_dpp<0x4E>(tot);   // quad_perm 2,3,0,1
+      tot = min_dpp<0x141>(tot);  // row_half_mirror
+      if (Gs > 8) {
+        tot = min_dpp<0x140>(tot);  // row_mirror
+        tot = min_shfl(tot, 16);
+        tot = min_shfl(tot, 32);
       }
-      __syncthreads();
-      for (int q = t; q < Gs * Q; q += B) {
-        const int g = q / Q;
-        sG[q] = sP[(g * N + sGn[g]) * Q + (q - g * Q)];
+      if (ls < Q) {
+        tb = sP[rows + (int)(uint32_t)tot * Q];
+#pragma unroll
+        for (int r = 0; r < R; ++r) gb[r] = sP[rows + (int)(uint32_t)best[r] * Q];
       }
-      __syncthreads();
       k += 1;
     }
     ctr += pending ? 1u : 0u;
     pending = fit ? 1 : 0;
   }
 
-  float4* Xo = reinterpret_cast<float4*>(s.X) + r0;
-  float4* Vo = reinterpret_cast<float4*>(s.V) + r0;
-  float4* Po = reinterpret_cast<float4*>(s.P) + r0;
-  float4* Go = reinterpret_cast<float4*>(s.gbest_pos) + (int64_t)g0 * Q;
-  for (int q = t; q < nS * Q; q += B) {
-    Xo[q] = sX[q];
-    Vo[q] = sV[q];
-    Po[q] = sP[q];
-  }
-  for (int q = t; q < Gs * Q; q += B) Go[q] = sG[q];
-  for (int i = t; i < nS; i += B) {
-    s.Pf[(int64_t)g0 * N + i] = sPf[i];
-    s.f[(int64_t)g0 * N + i] = sF[i];
-  }
-  for (int g = t; g < Gs; g += B) {
-    s.gbest_f[g0 + g] = sGf[g];
-    s.gbest_n[g0 + g] = sGn[g];
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    const int64_t q = r0 + (int64_t)id[r] * Q + ls;
+    if (row[r]) {
+      reinterpret_cast<float4*>(s.X)[q] = x4[r];
+      reinterpret_cast<float4*>(s.V)[q] = v4[r];
+      reinterpret_cast<float4*>(s.P)[q] = p4[r];
+      if (n_fit > 0 && id[r] == grp[r] * N)  // a group's first particle writes its best
+        reinterpret_cast<float4*>(s.gbest_pos)[(int64_t)(g0 + grp[r]) * Q + ls] = gb[r];
+    }
+    if (own[r]) {
+      s.Pf[(int64_t)g0 * N + id[r]] = pf[r];
+      s.f[(int64_t)g0 * N + id[r]] = fv[r];
+      if (n_fit > 0 && id[r] == grp[r] * N) {
+        s.gbest_f[g0 + grp[r]] = bf_key_f(best[r]);
+        s.gbest_n[g0 + grp[r]] = (int)(uint32_t)best[r] - grp[r] * N;
+      }
+    }
   }
 }
 
@@ -521,15 +608,28 @@ __global__ void bf_ctl_kernel(BFDev s, int n_fit, int flush) {
   *s.ctl = c;
 }
 
+// Rows of at most 256 floats, and Pbest rows (twice) and random factors within
+// 64 KiB of LDS with at most three particles per lane group.  Up to there the
+// one-launch run is the faster path whatever the swarms' number: an iteration
+// costs 0.6-3 us against 8.6 us or more for the two launches.
 bool bf_run_fits(const BFDev& s) {
-  return s.Dp <= 256 && bf_run_lds(s.Gs, s.N, s.Dp).bytes <= 64 * 1024;
+  const BFRunPlan r = bf_run_plan(s.Gs, s.N, s.Dp);
+  return s.Dp <= 256 && r.bytes <= kBFRunMax && r.R <= 3;
 }
 
 template <int FUNC>
 void launch_bf_run_f(const BFDev& s, int n_fit, int flush, hipStream_t st) {
-  const BFRunLds r = bf_run_lds(s.Gs, s.N, s.Dp);
-  hipLaunchKernelGGL((bf_run_kernel<FUNC>), dim3(s.S), dim3(kBFRunThreads), r.bytes, st, s, n_fit, flush,
-                     r.L);
+  const BFRunPlan r = bf_run_plan(s.Gs, s.N, s.Dp);
+  const dim3 grid(s.S), blk(r.threads);
+  // Griewank's last rounding: swarms that this path has always run keep two
+  const size_t nS = (size_t)s.Gs * s.N;
+  const int fused = 16 * (3 * nS * r.Q + (size_t)s.Gs * r.Q) + 4 * (7 * nS + 10 * (size_t)s.Gs) > 64 * 1024;
+  if (r.R == 1)
+    hipLaunchKernelGGL((bf_run_kernel<FUNC, 1>), grid, blk, r.bytes, st, s, n_fit, flush, r.L, r.ahead, fused);
+  else if (r.R == 2)
+    hipLaunchKernelGGL((bf_run_kernel<FUNC, 2>), grid, blk, r.bytes, st, s, n_fit, flush, r.L, r.ahead, fused);
+  else
+    hipLaunchKernelGGL((bf_run_kernel<FUNC, 3>), grid, blk, r.bytes, st, s, n_fit, flush, r.L, r.ahead, fused);
 }
 
 // n_fit evaluated iterations (then a flush move when flush) of every swarm,
