@@ -656,6 +656,52 @@ hipError_t enqueue_iteration(sepso_batch* b, int flags, bool fork, hipEvent_t be
   return e;
 }
 
+// Whether a frame's iterations go out as one launch, a workgroup per instance
+// (frame_kernel), and that launch.  It has to fit: one tile plan with K <= 12,
+// every swarm within a CU's LDS, no edge-by-edge polygons and one random
+// triple per particle.  And it has to pay, by the estimates below (us per
+// iteration, fitted to measured frames; within a fifth of them):
+//  - one workgroup: 3 us of barriers and bests, plus its waves' instructions
+//    in the crossing phase, 350 + 20 K + (5 K + 25) per rectangle + 20 K per
+//    convex polygon, at 2.5 ns each and one wave per SIMD at a time;
+//  - two launches: 11 us, plus the swarms' rows at the memory's rate or the
+//    same instructions on all CUs.
+// Measured, 8 x 32 particles of 20 waypoints and 4 rectangles: 7.7 us against
+// 12 for one instance, 8.1 against 24 for 256, 35 against 66 for 1024; with
+// 10 rectangles one instance takes 13 against 12 and keeps the two launches.
+bool frame_plan(const sepso_batch* b, FrameLaunch* f) {
+  if (b->buckets.size() != 1) return false;
+  const sepso_tune& tu = b->buckets[0].tune;
+  const int K = tu.seg_per_thread;
+  if (K > 12) return false;
+  f->block = tu.block_threads / b->buckets[0].pl.rsplit;
+  int blocks = 1, parts = 8;
+  for (const InstDesc& d : b->desc) blocks = std::max(blocks, d.n_blocks);
+  f->threads = std::min(blocks * f->block, kFrameThreads / f->block * f->block);
+  f->one = blocks * f->block <= f->threads;
+  double longest = 0.0, wg = 0.0, launches = 0.0;
+  for (const InstDesc& d : b->desc) {
+    if (d.n_gedges || d.rand_per_dim) return false;
+    const int nP = d.G * d.N;
+    f->one = f->one && nP <= f->threads;
+    parts = std::min(parts, std::max(1, f->threads / nP));
+    const double insts = 350.0 + 20.0 * K + (5.0 * K + 25.0) * d.n_rects + 20.0 * K * d.n_cpolys;
+    const int work = d.n_blocks * f->block, passes = (work + f->threads - 1) / f->threads;
+    const double us = 3.0 + passes * ((f->threads + 255) / 256) * insts * 2.5e-3;
+    longest = std::max(longest, us);
+    wg += us / kCUs;
+    launches += std::max(nP * 2.0 * d.W * 1e-3, work / 64.0 * insts * 0.5e-3) / kCUs;
+  }
+  for (f->ahead = parts;; f->ahead /= 2) {
+    f->lds = 0;
+    for (const InstDesc& d : b->desc)
+      f->lds = std::max(f->lds, frame_lds_bytes(d.G, d.N, d.W, f->threads, f->ahead));
+    if (f->lds <= (size_t)kFrameLdsMax || f->ahead == 1) break;
+  }
+  if (f->lds > (size_t)kFrameLdsMax) return false;
+  return 1.05 * std::max(longest, wg) < 11.0 + launches;
+}
+
 // Enqueue one whole frame of every instance; the first error of the
 // enqueued work (launch errors included).
 hipError_t enqueue_frame(sepso_batch* b, bool move) {
@@ -665,8 +711,14 @@ hipError_t enqueue_frame(sepso_batch* b, bool move) {
   int tmax = 0;
   for (auto& d : b->desc) tmax = std::max(tmax, d.T);
   hipError_t e = hipSuccess;
-  for (int k = 0; k < tmax && e == hipSuccess; ++k)
-    e = enqueue_iteration(b, STEP_FIT | STEP_FRAME, true);
+  FrameLaunch fl;
+  if (frame_plan(b, &fl)) {
+    const TileBucket& bk = b->buckets[0];
+    if (!launch_frame(bk.pl, bk.tune.seg_per_thread, fl, b->n, tmax, b->stream)) e = hipErrorInvalidValue;
+  } else {
+    for (int k = 0; k < tmax && e == hipSuccess; ++k)
+      e = enqueue_iteration(b, STEP_FIT | STEP_FRAME, true);
+  }
   if (e == hipSuccess)
     e = hipMemcpyAsync(b->h_ctl, b->pl.ctl, sizeof(InstCtl) * b->n, hipMemcpyDeviceToHost,
                        b->stream);

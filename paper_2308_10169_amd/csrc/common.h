@@ -182,6 +182,10 @@ struct EvolveDev {
   float* hyper_out;            // lower-level hyper rows (n x Dh), or null: the batch's hyper pool
 };
 
+// The whole-frame kernel: threads of a workgroup, LDS it may take.
+constexpr int kFrameThreads = 512;
+constexpr int kFrameLdsMax = 159 * 1024;
+
 // Kernel flags of the fused iteration.
 enum : int32_t { STEP_FIT = 1, STEP_FRAME = 2 };
 

@@ -10,6 +10,8 @@
 //   update_kernel -- the pending update alone (end of a stepping call);
 //   reduce_kernel -- per instance: group and total bests, Auto Truncation,
 //                    the online self-evolution step, control advance;
+//   frame_kernel  -- all iterations of a frame of a small instance, one
+//                    workgroup each;
 //   evolve_*      -- the evolution phase's higher level (H-SEPSO).
 #include "common.h"
 #include "kernels.h"
@@ -1133,6 +1135,340 @@ __global__ __launch_bounds__(256) void update_kernel(Pools pl, int flags) {
 }
 
 // ---------------------------------------------------------------------------
+// A whole frame of a small instance in one workgroup: all its iterations --
+// update, fitness, Pbest, group and total bests, Auto Truncation, the online
+// outer step -- in one launch with the swarm in LDS, where the two launches
+// per iteration of the kernels above cost a small swarm their latency (a chain
+// of memory round trips each) and its rows' way to memory and back.  Bound by
+// the CU's issue: about 1500 instructions per wave and iteration at 8 x 32
+// particles of 20 waypoints and 4 rectangles.
+//
+// The arithmetic and its order are those of iter_kernel and reduce_kernel:
+// the same chunks of K segments, the same blocks of ppb particles and so the
+// same waves in the crossing phase (a block is B of the workgroup's threads,
+// one wave group where the tile deals the rectangles over several; more
+// blocks than fit take turns), the update's sum pinned to the fused
+// multiply-adds the compiler forms there.  Results are bit-identical.
+//
+// Update and row copies give a thread one particle and a stretch of its
+// coordinate pairs: the particle's factors stay in registers, and rows lie
+// W | 1 pairs apart, so that the lanes' pairs fall into different banks (a
+// row of 2W floats apart, 64 lanes of a point fetch met on as few as 8).
+//
+// 256 instances of 8 x 32 particles, 20 waypoints, 4 rectangles: 8.1 us per
+// iteration (two launches: 24), 1360 VALU instructions per wave, issue 0.55 of
+// the SIMDs' cycles at the two waves each that one instance per CU gives.
+// ---------------------------------------------------------------------------
+__host__ __device__ inline int frame_row(int W) { return 2 * (W | 1); }
+
+inline size_t frame_lds_words(int G, int N, int W, int threads, int ahead) {
+  const size_t nP = (size_t)G * N, DS = frame_row(W);
+  return (3 * nP + G + 1) * DS + (7 + 3 * (size_t)ahead) * nP + 9 * (size_t)G + kHist + 2 * (size_t)threads + 4;
+}
+
+template <int K, bool ONE>
+__global__ __launch_bounds__(kFrameThreads) void frame_kernel(Pools pl, int B, int iters, int ahead) {
+  extern __shared__ __attribute__((aligned(16))) float s_dyn[];
+  const int inst = blockIdx.x;
+  InstDesc d = pl.desc[inst];  // by value: stores cannot make it reload
+  d.n_gedges = 0;              // no edge-by-edge polygons on this path
+  InstCtl* ctl = pl.ctl + inst;
+  if (ctl->done) return;
+  const int tid = threadIdx.x, T = blockDim.x;
+  const int G = d.G, N = d.N, W = d.W, D = 2 * W, S = W + 2, nP = G * N, DS = frame_row(W);
+  float* s_x = s_dyn;
+  float* s_v = s_x + nP * DS;
+  float* s_p = s_v + nP * DS;
+  float* s_gb = s_p + nP * DS;  // Tbest row, then the gbest rows
+  float* s_pf = s_gb + (G + 1) * DS;
+  float* s_f = s_pf + nP;
+  float* s_L = s_f + nP;
+  float* s_PL = s_L + nP;
+  int* s_Q = reinterpret_cast<int*>(s_PL + nP);
+  int* s_PQ = s_Q + nP;
+  int* s_imp = s_PQ + nP;
+  float* s_h = reinterpret_cast<float*>(s_imp + nP);  // hyper rows, then each group's inertia slope
+  float* s_gf = s_h + 7 * G;
+  int* s_gn = reinterpret_cast<int*>(s_gf + G);
+  float* s_hist = reinterpret_cast<float*>(s_gn + G);
+  int* s_q = reinterpret_cast<int*>(s_hist + kHist);
+  float* s_l = reinterpret_cast<float*>(s_q + T);
+  float* s_r = s_l + T;  // per iteration ahead and particle: r1, r2, r3
+  int* s_flag = reinterpret_cast<int*>(s_r + 3 * nP * ahead);  // stop, truncated
+
+  int k = ctl->k, pending = ctl->pending;
+  uint32_t ctr = ctl->ctr;
+  const float4 ends = pl.ends[inst];
+  for (int e = tid; e < nP * D; e += T) {
+    const int i = e / D, o = i * DS + (e - i * D);
+    s_x[o] = pl.X[d.xo + e];
+    s_v[o] = pl.V[d.xo + e];
+    s_p[o] = pl.P[d.xo + e];
+  }
+  for (int i = tid; i < nP; i += T) {
+    s_pf[i] = pl.Pf[d.po + i];
+    s_PL[i] = pl.PL[d.po + i];
+    s_PQ[i] = pl.PQ[d.po + i];
+  }
+  auto load_hyper = [&]() {
+    const float* h = pl.hyper + d.go * 6;
+    for (int e = tid; e < 6 * G; e += T) s_h[e] = h[e];
+    for (int g = tid; g < G; g += T) s_h[6 * G + g] = (h[6 * g + 3] - h[6 * g + 4]) / (float)d.T;
+  };
+  load_hyper();
+  if (pending)  // a move owed at the start takes the bests' rows from memory
+    for (int e = tid; e < (G + 1) * D; e += T) {
+      const int g = e / D, dd = e - g * D;
+      s_gb[g * DS + dd] = g == 0 ? pl.tbest_pos[d.dpo + dd] : pl.gbest_pos[d.gpo + (g - 1) * D + dd];
+    }
+  for (int i = tid; i < kHist; i += T) s_hist[i] = ctl->hist[i];
+  __syncthreads();
+
+  // this thread's share of a particle: pairs [q0, q1) of its W
+  const int parts = T > nP ? T / nP : 1;
+  const int part = tid / nP, q0 = part * W / parts, q1 = part < parts ? (part + 1) * W / parts : q0;
+  const int sub = tid / B, t = tid - sub * B, nsub = T / B;
+  const int C = (W + K) / K;
+  const int c = t / d.ppb, jt = t - c * d.ppb;
+  const int lane = tid & 63, wave = tid >> 6, n_waves = T >> 6;
+  const int i1 = tid - part * nP, gi1 = i1 / N;  // its first particle and group
+  const int eg = tid / W, eq = tid - eg * W;     // its first pair of the bests' rows
+  int drawn = 0;                                 // iterations whose factors are still in s_r
+  bool stop = false, at = false;
+  int tg = 0, tn = 0;
+  float tf = 0.f;
+  for (int it = 0; it < iters && !stop; ++it) {
+    // ---- previous iteration's update -----------------------------------------
+    if (pending) {
+      const int kk = k < d.T ? k : d.T;
+      if (drawn == 0) {  // a particle's parts draw for one of the next `ahead` moves each
+        drawn = ahead;
+        if (part < ahead)
+          for (int i = i1; i < nP; i += T) {
+            const U4 r = philox((uint32_t)i, ctr + (uint32_t)part, d.instance, TAG_UPDATE, d.seed_lo, d.seed_hi);
+            float* o = s_r + 3 * (part * nP + i);
+            o[0] = u01(r.v[0]);
+            o[1] = u01(r.v[1]);
+            o[2] = u01(r.v[2]);
+          }
+        if (ahead > 1) __syncthreads();
+      }
+      const float* rr = s_r + 3 * (ahead - drawn) * nP;
+      --drawn;
+      for (int i = i1; i < nP && q0 < q1; i += T) {
+        const int g = ONE || i == i1 ? gi1 : i / N;
+        const float* h = s_h + 6 * g;
+        const float a1 = h[0] * rr[3 * i], a2 = h[1] * rr[3 * i + 1], a3 = h[2] * rr[3 * i + 2];
+        const float w = fmaf(-s_h[6 * G + g], (float)kk, h[3]), vlh = h[5] * 0.5f;
+        float2* x2 = reinterpret_cast<float2*>(s_x + i * DS);
+        float2* v2 = reinterpret_cast<float2*>(s_v + i * DS);
+        const float2* p2 = reinterpret_cast<const float2*>(s_p + i * DS);
+        const float2* g2 = reinterpret_cast<const float2*>(s_gb + (g + 1) * DS);
+        const float2* t2 = reinterpret_cast<const float2*>(s_gb);
+        auto move = [&](float& x, float& v, float p, float gx, float tx, float hi) {
+          const float vmax = vlh * hi;
+          v = fmaf(a3, tx - x, fmaf(a2, gx - x, fmaf(w, v, a1 * (p - x))));
+          v = clampf(v, -vmax, vmax);
+          x = clampf(x + v, 0.f, hi);
+        };
+#pragma unroll 2
+        for (int q = q0; q < q1; ++q) {
+          float2 x = x2[q], v = v2[q];
+          const float2 p = p2[q], gx = g2[q], tx = t2[q];
+          move(x.x, v.x, p.x, gx.x, tx.x, 2 * q < W ? d.width : d.height);
+          move(x.y, v.y, p.y, gx.y, tx.y, 2 * q + 1 < W ? d.width : d.height);
+          x2[q] = x;
+          v2[q] = v;
+        }
+      }
+      __syncthreads();
+    }
+
+    // ---- fitness, block by block of ppb particles ------------------------------
+    for (int b0 = 0; b0 < (ONE ? 1 : d.n_blocks); b0 += nsub) {
+      const int p0 = (b0 + sub) * d.ppb;
+      const int np = min(d.ppb, nP - p0);  // <= 0: no block for these threads
+      const bool active = c < C && jt < np;
+      const int i0 = c * K;
+      float px[K + 1], py[K + 1];
+      const float* sx = s_x + (active ? p0 + jt : 0) * DS;
+#pragma unroll
+      for (int s = 0; s <= K; ++s) {
+        const int idx = min(i0 + s, S - 1);
+        const int wi = min(max(idx - 1, 0), W - 1);
+        const bool tgt = idx == S - 1;
+        float x = sx[wi], y = sx[W + wi];
+        x = tgt ? ends.z : x;
+        y = tgt ? ends.w : y;
+        if (s == 0) {
+          x = idx == 0 ? ends.x : x;
+          y = idx == 0 ? ends.y : y;
+        }
+        px[s] = x;
+        py[s] = y;
+      }
+      float dx[K], ndy[K], nc[K];
+      float len_sum = 0.f;
+#pragma unroll
+      for (int s = 0; s < K; ++s) {
+        const float ddx = px[s + 1] - px[s], ddy = py[s + 1] - py[s];
+        const bool seg = active && i0 + s < S - 1;
+        dx[s] = seg ? ddx : 0.f;
+        ndy[s] = seg ? -ddy : 0.f;
+        nc[s] = seg ? fmaf(ddy, px[s], -(ddx * py[s])) : 0.f;
+        if (seg) len_sum += __builtin_amdgcn_sqrtf(fmaf(ddx, ddx, ddy * ddy));
+      }
+      int ct = 0;
+      crossings<K, 1>(pl, d, nullptr, active, 0, px, py, dx, ndy, nc, ct);
+      s_q[tid] = ct;
+      s_l[tid] = len_sum;
+      __syncthreads();
+      if (t < np) {
+        int q = 0;
+        float L = 0.f;
+        const int s0 = sub * B + t;
+        for (int cc = 0; cc < C; ++cc) {
+          q += s_q[s0 + cc * d.ppb];
+          L += s_l[s0 + cc * d.ppb];
+        }
+        const float qf = (float)q;
+        float pw = 1.f;
+        for (int b = 0; b < d.beta; ++b) pw *= qf;
+        const float fv = fmaf(d.alpha, pw, L);
+        const int i = p0 + t;
+        s_f[i] = fv;
+        s_L[i] = L;
+        s_Q[i] = q;
+        const float fc = isfinite(fv) ? fv : INFINITY;
+        const int imp = fc < s_pf[i];
+        if (imp) {
+          s_pf[i] = fc;
+          s_PL[i] = L;
+          s_PQ[i] = q;
+        }
+        s_imp[i] = imp;
+      }
+      __syncthreads();
+    }
+    // improved particles' rows; meanwhile the groups' bests (one wave each)
+    for (int i = i1; i < nP && q0 < q1; i += T)
+      if (s_imp[i]) {
+        const float2* x2 = reinterpret_cast<const float2*>(s_x + i * DS);
+        float2* p2 = reinterpret_cast<float2*>(s_p + i * DS);
+        for (int q = q0; q < q1; ++q) p2[q] = x2[q];
+      }
+    for (int g = wave; g < G; g += n_waves) {
+      float bf = INFINITY;
+      int bn = 0x7fffffff;
+      for (int n = lane; n < N; n += 64)
+        if (better(s_pf[g * N + n], n, bf, bn)) {
+          bf = s_pf[g * N + n];
+          bn = n;
+        }
+#pragma unroll
+      for (int m = 32; m > 0; m >>= 1) {
+        const float of = __shfl_xor(bf, m);
+        const int on = __shfl_xor(bn, m);
+        if (better(of, on, bf, bn)) {
+          bf = of;
+          bn = on;
+        }
+      }
+      if (lane == 0) {
+        s_gn[g] = bn < N ? bn : 0;
+        s_gf[g] = bf;
+      }
+    }
+    __syncthreads();
+    {
+      // total best: the lowest group of the lowest fitness (never NaN, nor -0:
+      // lengths and penalties are not negative)
+      const float gf = lane < G ? s_gf[lane] : INFINITY;
+      const int gk = float_key(gf), lo = wave_min_key(gk);
+      tg = (int)__builtin_ctzll(__builtin_amdgcn_ballot_w64(lane < G && gk == lo));
+    }
+    tn = s_gn[tg];
+    tf = s_gf[tg];
+    for (int e = tid; e < (G + 1) * W; e += T) {  // pairs of the bests' rows
+      const int g = e == tid ? eg : e / W, q = e == tid ? eq : e - g * W;
+      const int i = g == 0 ? tg * N + tn : (g - 1) * N + s_gn[g - 1];
+      reinterpret_cast<float2*>(s_gb + g * DS)[q] = reinterpret_cast<const float2*>(s_p + i * DS)[q];
+    }
+    const int k_new = k + 1;
+    if (tid == 0) {
+      s_hist[(k_new - 1) % kHist] = tf;
+      const bool a = at_fires(s_hist, k_new, d.at_mode, d.at_window, d.at_delta, s_PQ[tg * N + tn]);
+      s_flag[0] = a || k_new >= d.T;
+      s_flag[1] = a;
+    }
+    __syncthreads();
+    stop = s_flag[0];
+    at = s_flag[1];
+    if (!stop && d.hsef_every > 0 && k_new % d.hsef_every == 0) {
+      hsef_step(pl, d, ctl, s_gf);
+      load_hyper();
+      __syncthreads();
+    }
+    k = k_new;
+    ctr += pending ? 1u : 0u;
+    pending = 1;
+  }
+
+  // ---- the state as the last iteration's launches leave it ---------------------
+  for (int e = tid; e < nP * D; e += T) {
+    const int i = e / D, o = i * DS + (e - i * D);
+    pl.X[d.xo + e] = s_x[o];
+    pl.V[d.xo + e] = s_v[o];
+    pl.P[d.xo + e] = s_p[o];
+  }
+  for (int i = tid; i < nP; i += T) {
+    pl.f[d.po + i] = s_f[i];
+    pl.L[d.po + i] = s_L[i];
+    pl.Q[d.po + i] = s_Q[i];
+    pl.Pf[d.po + i] = s_pf[i];
+    pl.PL[d.po + i] = s_PL[i];
+    pl.PQ[d.po + i] = s_PQ[i];
+  }
+  for (int e = tid; e < (G + 1) * D; e += T) {
+    const int g = e / D, dd = e - g * D;
+    const float x = s_gb[g * DS + dd];
+    if (g == 0) {
+      pl.tbest_pos[d.dpo + dd] = x;
+      if (stop) pl.prev_path[d.dpo + dd] = x;
+    } else {
+      pl.gbest_pos[d.gpo + (g - 1) * D + dd] = x;
+    }
+  }
+  for (int g = tid; g < G; g += T) {
+    pl.gbest_n[d.go + g] = s_gn[g];
+    pl.gbest_f[d.go + g] = s_gf[g];
+  }
+  for (int i = tid; i < kHist; i += T) ctl->hist[i] = s_hist[i];
+  if (tid == 0) {
+    ctl->k = k;
+    ctl->tb_g = tg;
+    ctl->tb_n = tn;
+    ctl->tb_f = tf;
+    if (stop) {
+      ctl->done = 1;
+      ctl->pending = 0;
+      ctl->ctr = ctr + 1u;
+      ctl->truncated = at;
+      ctl->res_cost = tf;
+      ctl->res_len = s_PL[tg * N + tn];
+      ctl->res_q = s_PQ[tg * N + tn];
+      ctl->res_iters = k;
+      ctl->res_trunc = at;
+      ctl->have_prev = 1;
+      ctl->frame += 1;
+    } else {
+      ctl->pending = 1;
+      ctl->ctr = ctr;
+    }
+  }
+}
+
+// ---------------------------------------------------------------------------
 void launch_geom(const Pools& pl, int n_inst, int move, hipStream_t s) {
   hipLaunchKernelGGL(geom_kernel, dim3(n_inst), dim3(256), 0, s, pl, move);
 }
@@ -1175,6 +1511,29 @@ bool launch_tiles(const Pools& pl, int K, int n_blocks, int threads, int flags, 
     case 12: launch_tiles_k<12>(pl, n_blocks, threads, flags, s); return true;
     case 16: launch_tiles_k<16>(pl, n_blocks, threads, flags, s); return true;
     case 24: launch_tiles_k<24>(pl, n_blocks, threads, flags, s); return true;
+    default: return false;
+  }
+}
+
+size_t frame_lds_bytes(int G, int N, int W, int threads, int ahead) {
+  return 4 * frame_lds_words(G, N, W, threads, ahead);
+}
+
+template <int K, bool ONE>
+static bool launch_frame_k(const Pools& pl, const FrameLaunch& f, int n_inst, int iters, hipStream_t s) {
+  // past 64 KiB of dynamic LDS a kernel has to be told
+  if (hipFuncSetAttribute(reinterpret_cast<const void*>(frame_kernel<K, ONE>),
+                          hipFuncAttributeMaxDynamicSharedMemorySize, kFrameLdsMax) != hipSuccess)
+    return false;
+  hipLaunchKernelGGL((frame_kernel<K, ONE>), dim3(n_inst), dim3(f.threads), f.lds, s, pl, f.block, iters, f.ahead);
+  return true;
+}
+
+bool launch_frame(const Pools& pl, int K, const FrameLaunch& f, int n_inst, int iters, hipStream_t s) {
+  switch (K) {
+    case 4: return f.one ? launch_frame_k<4, true>(pl, f, n_inst, iters, s) : launch_frame_k<4, false>(pl, f, n_inst, iters, s);
+    case 8: return f.one ? launch_frame_k<8, true>(pl, f, n_inst, iters, s) : launch_frame_k<8, false>(pl, f, n_inst, iters, s);
+    case 12: return f.one ? launch_frame_k<12, true>(pl, f, n_inst, iters, s) : launch_frame_k<12, false>(pl, f, n_inst, iters, s);
     default: return false;
   }
 }
