@@ -17,6 +17,7 @@ constexpr int kStageFloats = 2048;  // general-polygon edge records staged in LD
 constexpr int kRaster = 64;
 constexpr int kLinIn = kRaster * kRaster + 4;   // 4100
 constexpr int kLinInPad = 4128;                 // multiple of 32
+constexpr int kLinInLd = 4160;                  // its rows' distance: whole 128-byte lines of BF16
 constexpr int kLinHidden = 512;
 constexpr int kLinGroups = 8, kLinW = 20;
 constexpr int kLinOut = kLinGroups * 2 * kLinW; // 320

@@ -96,22 +96,22 @@ struct sepso_lin {
   float* W32[4];
   float* b32[4];
   uint16_t* W16[4];
+  uint16_t* WT[4];   // W16 transposed (layers 1..3; the first layer's input gradient is not taken)
   float *mW[4], *vW[4], *mb[4], *vb[4];
   float* gW[4];
   float* gb[4];
-  uint16_t* X16;     // max_rows x kLinInPad
+  uint16_t* X16;     // max_rows x kLinInLd
   uint16_t* A16[3];  // max_rows x 512
   float* Y;          // max_rows x 320
   float* T;          // max_rows x 320
-  float* dY;
   uint16_t* dY16;
   float* dZ[3];
   uint16_t* dZ16[3];
   float* rowsq;
   float* dloss;       // loss per training step
-  float* splitk;      // split-K GEMM slices
+  float* colpart[4];  // bias gradients' partial column sums
   int32_t* eligible;  // max_rows
-  uint16_t* DX;       // max_samples x kLinInPad
+  uint16_t* DX;       // max_samples x kLinInLd
   float* DT;          // max_samples x 320
   float* h_loss = nullptr;  // pinned, max_rows
 };

@@ -17,11 +17,10 @@ using namespace sepso;
 namespace {
 
 const int kInPad[4] = {kLinInPad, kLinHidden, kLinHidden, kLinHidden};
+const int kInLd[4] = {kLinInLd, kLinHidden, kLinHidden, kLinHidden};  // rows' distance, BF16
 const int kInReal[4] = {kLinIn, kLinHidden, kLinHidden, kLinHidden};
 const int kOutN[4] = {kLinHidden, kLinHidden, kLinHidden, kLinOut};
 constexpr int kLossHist = 1 << 16;
-// split-K slices (FP32): up to four of the layer-1 weight gradient
-constexpr int64_t kSplitWs = 4 * kLinHidden * kLinInPad;
 
 int64_t n_params() {
   int64_t n = 0;
@@ -45,16 +44,19 @@ size_t lin_layout(int max_rows, int64_t max_samples, sepso_lin* L, char* base) {
     char* p;
     p = take(4 * nw); if (L) L->W32[l] = (float*)p;
     p = take(4 * nb); if (L) L->b32[l] = (float*)p;
-    p = take(2 * nw); if (L) L->W16[l] = (uint16_t*)p;
+    p = take(2 * (size_t)kOutN[l] * kInLd[l]); if (L) L->W16[l] = (uint16_t*)p;
+    if (l > 0) p = take(2 * nw);
+    if (L) L->WT[l] = l > 0 ? (uint16_t*)p : nullptr;
     p = take(4 * nw); if (L) L->mW[l] = (float*)p;
     p = take(4 * nw); if (L) L->vW[l] = (float*)p;
     p = take(4 * nb); if (L) L->mb[l] = (float*)p;
     p = take(4 * nb); if (L) L->vb[l] = (float*)p;
     p = take(4 * nw); if (L) L->gW[l] = (float*)p;
     p = take(4 * nb); if (L) L->gb[l] = (float*)p;
+    p = take(4 * (size_t)col_part_floats(max_rows)); if (L) L->colpart[l] = (float*)p;
   }
   char* p;
-  p = take(2 * (size_t)max_rows * kLinInPad); if (L) L->X16 = (uint16_t*)p;
+  p = take(2 * (size_t)max_rows * kLinInLd); if (L) L->X16 = (uint16_t*)p;
   for (int l = 0; l < 3; ++l) {
     p = take(2 * (size_t)max_rows * kLinHidden); if (L) L->A16[l] = (uint16_t*)p;
     p = take(4 * (size_t)max_rows * kLinHidden); if (L) L->dZ[l] = (float*)p;
@@ -62,13 +64,11 @@ size_t lin_layout(int max_rows, int64_t max_samples, sepso_lin* L, char* base) {
   }
   p = take(4 * (size_t)max_rows * kLinOut); if (L) L->Y = (float*)p;
   p = take(4 * (size_t)max_rows * kLinOut); if (L) L->T = (float*)p;
-  p = take(4 * (size_t)max_rows * kLinOut); if (L) L->dY = (float*)p;
   p = take(2 * (size_t)max_rows * kLinOut); if (L) L->dY16 = (uint16_t*)p;
   p = take(4 * (size_t)max_rows); if (L) L->rowsq = (float*)p;
   p = take(4 * (size_t)max_rows); if (L) L->eligible = (int32_t*)p;
   p = take(4 * (size_t)kLossHist); if (L) L->dloss = (float*)p;
-  p = take(4 * (size_t)kSplitWs); if (L) L->splitk = (float*)p;
-  p = take(2 * (size_t)max_samples * kLinInPad); if (L) L->DX = (uint16_t*)p;
+  p = take(2 * (size_t)max_samples * kLinInLd); if (L) L->DX = (uint16_t*)p;
   p = take(4 * (size_t)max_samples * kLinOut); if (L) L->DT = (float*)p;
   return o;
 }
@@ -97,65 +97,59 @@ sepso_status lin_usable(sepso_lin* L) {
   return SEPSO_OK;
 }
 
-void forward(sepso_lin* L, const uint16_t* X, int M, hipStream_t s) {
+// Outputs Y of the M rows of X; with targets T also dY16, the gradient of the
+// mean squared error.
+void forward(sepso_lin* L, const uint16_t* X, int M, hipStream_t s, const float* T = nullptr) {
   const uint16_t* in = X;
-  int ldi = kLinInPad;
+  int ldi = kLinInLd;
   for (int l = 0; l < 3; ++l) {
-    const Epi ep{EPI_BIAS_RELU_BF16, L->b32[l], nullptr, L->A16[l], nullptr, kLinHidden};
-    launch_gemm(false, false, in, ldi, L->W16[l], kInPad[l], M, kLinHidden, kInPad[l], ep, L->splitk, kSplitWs, s);
+    const Epi ep{EPI_BIAS_RELU_BF16, L->b32[l], nullptr, L->A16[l], nullptr, kLinHidden, nullptr, 0.f};
+    launch_gemm(in, ldi, L->W16[l], kInLd[l], M, kLinHidden, kInPad[l], ep, s);
     in = L->A16[l];
     ldi = kLinHidden;
   }
-  const Epi ep{EPI_BIAS_F32, L->b32[3], L->Y, nullptr, nullptr, kLinOut};
-  launch_gemm(false, false, L->A16[2], kLinHidden, L->W16[3], kLinHidden, M, kLinOut, kLinHidden, ep, L->splitk, kSplitWs, s);
+  const Epi ep{T ? EPI_BIAS_LOSS : EPI_BIAS_F32, L->b32[3], L->Y, L->dY16, nullptr, kLinOut, T, 2.f / ((float)M * (float)kLinOut)};
+  launch_gemm(L->A16[2], kLinHidden, L->W16[3], kLinHidden, M, kLinOut, kLinHidden, ep, s);
 }
 
-// Gradients of the mean squared error for rows X (B rows) against targets T.
-void backward(sepso_lin* L, const uint16_t* X, const float* T, int B, float* loss_slot,
+// Gradients of the mean squared error for rows X (B rows) against targets T,
+// after forward() with these; with ad.on the parameters take the Adam step
+// instead of gW and gb the gradients.
+void backward(sepso_lin* L, const uint16_t* X, const float* T, int B, const AdamStep& ad, float* loss_slot,
               hipStream_t s) {
-  launch_loss(L->Y, T, B, kLinOut, L->dY, L->dY16, L->rowsq, s);
-  launch_loss_sum(L->rowsq, B, 1.f / ((float)B * kLinOut), loss_slot, s);
-  launch_colsum(L->dY, B, kLinOut, L->gb[3], L->splitk, s);
-  launch_gemm(true, true, L->dY16, kLinOut, L->A16[2], kLinHidden, kLinOut, kLinHidden, B,
-              Epi{EPI_F32, nullptr, L->gW[3], nullptr, nullptr, kLinHidden}, L->splitk, kSplitWs, s);
-  launch_gemm(false, true, L->dY16, kLinOut, L->W16[3], kLinHidden, B, kLinHidden, kLinOut,
-              Epi{EPI_MASK, nullptr, L->dZ[2], L->dZ16[2], L->A16[2], kLinHidden}, L->splitk, kSplitWs, s);
-  for (int l = 2; l >= 1; --l) {
-    launch_colsum(L->dZ[l], B, kLinHidden, L->gb[l], L->splitk, s);
-    launch_gemm(true, true, L->dZ16[l], kLinHidden, L->A16[l - 1], kLinHidden, kLinHidden,
-                kLinHidden, B, Epi{EPI_F32, nullptr, L->gW[l], nullptr, nullptr, kLinHidden}, L->splitk, kSplitWs, s);
-    launch_gemm(false, true, L->dZ16[l], kLinHidden, L->W16[l], kLinHidden, B, kLinHidden,
-                kLinHidden, Epi{EPI_MASK, nullptr, L->dZ[l - 1], L->dZ16[l - 1], L->A16[l - 1], kLinHidden}, L->splitk, kSplitWs, s);
+  for (int l = 3; l >= 1; --l) {
+    const Epi ep{EPI_MASK, nullptr, L->dZ[l - 1], L->dZ16[l - 1], L->A16[l - 1], kLinHidden, nullptr, 0.f};
+    launch_gemm(l == 3 ? L->dY16 : L->dZ16[l], kOutN[l], L->WT[l], kOutN[l], B, kLinHidden, kOutN[l], ep, s);
   }
-  launch_colsum(L->dZ[0], B, kLinHidden, L->gb[0], L->splitk, s);
-  launch_gemm(true, true, L->dZ16[0], kLinHidden, X, kLinInPad, kLinHidden, kLinInPad, B,
-              Epi{EPI_F32, nullptr, L->gW[0], nullptr, nullptr, kLinInPad}, L->splitk, kSplitWs, s);
+  DwArgs a{};
+  for (int l = 0; l < 4; ++l) {
+    a.w[l] = DwSet{l == 3 ? L->dY16 : L->dZ16[l], l == 0 ? X : L->A16[l - 1], kOutN[l], kInPad[l], kInLd[l], L->gW[l],
+                   L->W32[l], L->mW[l], L->vW[l], L->W16[l], L->WT[l], 0, 0};
+    a.c[l] = ColSet{l == 3 ? nullptr : L->dZ[l], kOutN[l], L->colpart[l], L->gb[l], L->b32[l], L->mb[l], L->vb[l], 0, 0};
+  }
+  a.K = B;
+  a.adam = ad;
+  a.y = L->Y;
+  a.target = T;
+  a.scale = 2.f / ((float)B * (float)kLinOut);
+  a.row_sq = L->rowsq;
+  launch_weight_grads(a, 1.f / ((float)B * kLinOut), loss_slot, s);
 }
 
-void adam(sepso_lin* L, float lr, hipStream_t s) {
+AdamStep adam_step(sepso_lin* L, float lr) {
   L->adam_t += 1;
   const float b1 = 0.9f, b2 = 0.999f, eps = 1e-8f;
   // bias corrections from the same (FP32) decay rates the moments use
   const float c1 = (float)(1.0 - std::pow((double)b1, L->adam_t));
   const float c2 = (float)(1.0 - std::pow((double)b2, L->adam_t));
-  // all eight tensors (weights and biases of the four layers) in one launch
-  AdamSets a{};
-  for (int l = 0; l < 4; ++l) {
-    const int w = 2 * l, b = 2 * l + 1;
-    a.p[w] = L->W32[l]; a.g[w] = L->gW[l]; a.m[w] = L->mW[l]; a.v[w] = L->vW[l];
-    a.p16[w] = L->W16[l]; a.count[w] = (int64_t)kOutN[l] * kInPad[l];
-    a.p[b] = L->b32[l]; a.g[b] = L->gb[l]; a.m[b] = L->mb[l]; a.v[b] = L->vb[l];
-    a.p16[b] = nullptr; a.count[b] = kOutN[l];
-  }
-  a.n = 8;
-  launch_adam_sets(a, lr, b1, b2, eps, c1, c2, s);
+  return AdamStep{1, lr, b1, b2, eps, c1, c2};
 }
 
-// Upload host FP32 rows (n x kLinIn) as BF16 rows of stride kLinInPad.
+// Upload host FP32 rows (n x kLinIn) as BF16 rows of stride kLinInLd.
 sepso_status upload_inputs(sepso_lin* L, const float* x, int n) {
-  std::vector<uint16_t> h((size_t)n * kLinInPad, 0);
+  std::vector<uint16_t> h((size_t)n * kLinInLd, 0);
   for (int r = 0; r < n; ++r)
-    for (int j = 0; j < kLinIn; ++j) h[(size_t)r * kLinInPad + j] = host_bf16(x[(size_t)r * kLinIn + j]);
+    for (int j = 0; j < kLinIn; ++j) h[(size_t)r * kLinInLd + j] = host_bf16(x[(size_t)r * kLinIn + j]);
   LHIP(L, hipMemcpyAsync(L->X16, h.data(), 2 * h.size(), hipMemcpyHostToDevice, L->stream));
   LHIP(L, hipStreamSynchronize(L->stream));
   return SEPSO_OK;
@@ -165,7 +159,7 @@ sepso_status upload_inputs(sepso_lin* L, const float* x, int n) {
 
 namespace sepso {
 void lin_enqueue_proposals(sepso_lin* L, sepso_batch* b) {
-  launch_raster(b->pl, b->n, L->X16, kLinInPad, L->eligible, b->stream);
+  launch_raster(b->pl, b->n, L->X16, kLinInLd, L->eligible, b->stream);
   forward(L, L->X16, b->n, b->stream);
   launch_proposal(b->pl, b->n, L->Y, kLinOut, L->eligible, b->stream);
 }
@@ -222,7 +216,7 @@ sepso_status sepso_lin_create(int32_t max_rows, int64_t max_samples, uint64_t se
         w[(size_t)o * kInPad[l] + i] = (float)(-a + 2.0 * a * ((next() >> 11) * (1.0 / 9007199254740992.0)));
     e = hipMemcpyAsync(L->W32[l], w.data(), 4 * w.size(), hipMemcpyHostToDevice, L->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(L->stream);
-    if (e == hipSuccess) launch_cvt_bf16(L->W32[l], L->W16[l], (int64_t)w.size(), L->stream);
+    if (e == hipSuccess) launch_cvt_bf16(L->W32[l], L->W16[l], kInLd[l], L->WT[l], kOutN[l], kInPad[l], L->stream);
   }
   if (e == hipSuccess) e = hipGetLastError();
   if (e == hipSuccess) e = hipHostMalloc((void**)&L->h_loss, 4 * kLossHist, hipHostMallocDefault);
@@ -263,7 +257,7 @@ sepso_status sepso_lin_set_weights(sepso_lin* L, const float* flat) {
     LHIP(L, hipMemcpyAsync(L->b32[l], p, 4 * kOutN[l], hipMemcpyHostToDevice, L->stream));
     p += kOutN[l];
     LHIP(L, hipStreamSynchronize(L->stream));
-    launch_cvt_bf16(L->W32[l], L->W16[l], (int64_t)w.size(), L->stream);
+    launch_cvt_bf16(L->W32[l], L->W16[l], kInLd[l], L->WT[l], kOutN[l], kInPad[l], L->stream);
   }
   LHIP(L, hipGetLastError());
   LHIP(L, hipStreamSynchronize(L->stream));
@@ -310,8 +304,8 @@ sepso_status sepso_lin_grads(sepso_lin* L, const float* x, const float* t, int32
   st = upload_inputs(L, x, n);
   if (st != SEPSO_OK) return st;
   LHIP(L, hipMemcpyAsync(L->T, t, 4 * (size_t)n * kLinOut, hipMemcpyHostToDevice, L->stream));
-  forward(L, L->X16, n, L->stream);
-  backward(L, L->X16, L->T, n, L->dloss, L->stream);
+  forward(L, L->X16, n, L->stream, L->T);
+  backward(L, L->X16, L->T, n, AdamStep{}, L->dloss, L->stream);
   LHIP(L, hipGetLastError());
   LHIP(L, hipMemcpyAsync(L->h_loss, L->dloss, 4, hipMemcpyDeviceToHost, L->stream));
   float* p = grads;
@@ -338,9 +332,9 @@ sepso_status sepso_lin_collect(sepso_lin* L, sepso_batch* b) {
     if (d.G != kLinGroups || d.W != kLinW)
       return fail(SEPSO_E_UNSUPPORTED, "collection needs %d groups of %d waypoints", kLinGroups, kLinW);
   if (L->n_samples + b->n > L->max_samples) return fail(SEPSO_E_NOMEM, "training set is full");
-  uint16_t* X = L->DX + (size_t)L->n_samples * kLinInPad;
+  uint16_t* X = L->DX + (size_t)L->n_samples * kLinInLd;
   float* T = L->DT + (size_t)L->n_samples * kLinOut;
-  launch_raster(b->pl, b->n, X, kLinInPad, L->eligible, b->stream);
+  launch_raster(b->pl, b->n, X, kLinInLd, L->eligible, b->stream);
   launch_targets(b->pl, b->n, T, kLinOut, b->stream);
   LHIP(L, hipGetLastError());
   LHIP(L, hipStreamSynchronize(b->stream));
@@ -364,11 +358,10 @@ sepso_status sepso_lin_train(sepso_lin* L, int32_t steps, int32_t batch, float l
   const int64_t nb = L->n_samples / batch;
   for (int s = 0; s < steps; ++s) {
     const int64_t slot = s % nb;
-    const uint16_t* X = L->DX + (size_t)slot * batch * kLinInPad;
+    const uint16_t* X = L->DX + (size_t)slot * batch * kLinInLd;
     const float* T = L->DT + (size_t)slot * batch * kLinOut;
-    forward(L, X, batch, L->stream);
-    backward(L, X, T, batch, L->dloss + s, L->stream);
-    adam(L, lr, L->stream);
+    forward(L, X, batch, L->stream, T);
+    backward(L, X, T, batch, adam_step(L, lr), L->dloss + s, L->stream);
   }
   LHIP(L, hipGetLastError());
   if (loss_out) {
@@ -384,14 +377,14 @@ sepso_status sepso_lin_features(sepso_lin* L, sepso_batch* b, float* out) {
   sepso_status st = lin_usable(L);
   if (st != SEPSO_OK) return st;
   if (!b || !out || b->n > L->max_rows) return fail(SEPSO_E_ARG, "batch/out NULL or batch too large");
-  launch_raster(b->pl, b->n, L->X16, kLinInPad, L->eligible, b->stream);
+  launch_raster(b->pl, b->n, L->X16, kLinInLd, L->eligible, b->stream);
   LHIP(L, hipGetLastError());
-  std::vector<uint16_t> h((size_t)b->n * kLinInPad);
+  std::vector<uint16_t> h((size_t)b->n * kLinInLd);
   LHIP(L, hipMemcpyAsync(h.data(), L->X16, 2 * h.size(), hipMemcpyDeviceToHost, b->stream));
   LHIP(L, hipStreamSynchronize(b->stream));
   for (int r = 0; r < b->n; ++r)
     for (int j = 0; j < kLinIn; ++j) {
-      const uint32_t u = (uint32_t)h[(size_t)r * kLinInPad + j] << 16;
+      const uint32_t u = (uint32_t)h[(size_t)r * kLinInLd + j] << 16;
       std::memcpy(&out[(size_t)r * kLinIn + j], &u, 4);
     }
   return SEPSO_OK;

@@ -6,7 +6,7 @@
 
 namespace sepso {
 
-enum : int { EPI_BIAS_RELU_BF16 = 0, EPI_BIAS_F32 = 1, EPI_F32 = 2, EPI_MASK = 3 };
+enum : int { EPI_BIAS_RELU_BF16 = 0, EPI_BIAS_F32 = 1, EPI_BIAS_LOSS = 2, EPI_MASK = 3 };
 
 // GEMM epilogue: what happens to each FP32 accumulator C(row, col).
 struct Epi {
@@ -16,34 +16,54 @@ struct Epi {
   uint16_t* out_bf16;    // row stride ldo
   const uint16_t* mask;  // ReLU mask source (BF16 activations), row stride ldo
   int ldo;
+  const float* target;   // EPI_BIAS_LOSS: row stride ldo; out_bf16 = scale * (C + bias - target)
+  float scale;
 };
 
 void launch_raster(const Pools& pl, int n_inst, uint16_t* X, int ldx, int32_t* eligible,
                    hipStream_t s);
-// ws: FP32 split-K workspace of ws_floats (S x M x N are used when K is split).
-void launch_gemm(bool a_km, bool b_kn, const uint16_t* A, int lda, const uint16_t* B, int ldb,
-                 int M, int N, int K, const Epi& ep, float* ws, int64_t ws_floats, hipStream_t s);
-void launch_loss(const float* y, const float* target, int B, int n, float* dy, uint16_t* dy16,
-                 float* row_sq, hipStream_t s);
-// ws: FP32 scratch of ceil(B / 256) x n (row-chunk partial sums).
-void launch_colsum(const float* dz, int B, int n, float* out, float* ws, hipStream_t s);
-void launch_loss_sum(const float* row_sq, int B, float scale, float* out, hipStream_t s);
+// C[M x N] = A[M x K] B[N x K]^T (k contiguous in both, K % 32 == 0, N % 32 == 0, 16-byte aligned rows).
+void launch_gemm(const uint16_t* A, int lda, const uint16_t* B, int ldb, int M, int N, int K, const Epi& ep,
+                 hipStream_t s);
 void launch_targets(const Pools& pl, int n_inst, float* T, int ldt, hipStream_t s);
-// Parameter tensors updated by one Adam launch (p16 may be NULL per set).
-constexpr int kAdamMaxSets = 8;
-struct AdamSets {
-  float* p[kAdamMaxSets];
-  const float* g[kAdamMaxSets];
-  float* m[kAdamMaxSets];
-  float* v[kAdamMaxSets];
-  uint16_t* p16[kAdamMaxSets];
-  int64_t count[kAdamMaxSets];
-  int64_t first_block[kAdamMaxSets];  // filled by launch_adam_sets
-  int n;
+
+struct AdamStep {
+  int on;  // 0: gradients are stored, parameters stay
+  float lr, b1, b2, eps, c1, c2;
 };
-void launch_adam_sets(AdamSets a, float lr, float b1, float b2, float eps, float c1, float c2,
-                      hipStream_t s);
-void launch_cvt_bf16(const float* p, uint16_t* p16, int64_t count, hipStream_t s);
+// One layer's weights: dW[M x N] = A^T B over the batch's K rows (A: K x M, B: K x N,
+// its rows and those of p16 ldb apart).
+struct DwSet {
+  const uint16_t *A, *B;
+  int M, N, ldb;
+  float *g, *p, *m, *v;  // gradient; parameters and moments (M x N)
+  uint16_t *p16, *pT;    // BF16 parameters, and transposed (N x M) or NULL
+  int kper, first;       // filled by launch_weight_grads
+};
+// The same layer's biases: column sums of its FP32 dZ (K x n; NULL: the last
+// layer's, from y and target).
+struct ColSet {
+  const float* dz;
+  int n;
+  float* part;  // scratch, col_part_floats of the largest K
+  float *g, *p, *m, *v;
+  int cr, first;  // filled by launch_weight_grads
+};
+struct DwArgs {
+  DwSet w[4];
+  ColSet c[4];
+  int K, tiles, col_blocks;
+  AdamStep adam;
+  const float *y, *target;  // K x kLinOut
+  float scale;              // dY = scale (y - target)
+  float* row_sq;            // K: squared errors per row
+};
+// Weight and bias gradients of all layers, the Adam step where a.adam.on, and
+// the loss (loss_scale times the sum of squared errors): two launches.
+void launch_weight_grads(DwArgs a, float loss_scale, float* loss, hipStream_t s);
+constexpr int64_t col_part_floats(int64_t max_rows) { return (max_rows / 256 + 256) * kLinHidden; }
+// BF16 copies of M x N weights: p16 (rows ld apart) and, transposed, pT (or NULL).
+void launch_cvt_bf16(const float* p, uint16_t* p16, int ld, uint16_t* pT, int M, int N, hipStream_t s);
 void launch_proposal(const Pools& pl, int n_inst, const float* Y, int ldy, const int32_t* eligible,
                      hipStream_t s);
 
