@@ -178,6 +178,15 @@ Layout plan_layout(const sepso_map* maps, const sepso_swarm* sw, int n, std::vec
       d.geo = (int32_t)L.sumGE;
       d.cpo = (int32_t)L.sumCP;
     }
+    // at most a slot per two particles (the smallest block) and per group
+    const int slots = n > kCandInsts ? 0 : (int)std::min<int64_t>(kCandSlots, P / 2 + 1 + G);
+    if (desc) {
+      (*desc)[i].slots = slots;
+      (*desc)[i].co = (int32_t)L.sumC;
+      (*desc)[i].cro = L.sumCR;
+    }
+    L.sumC += 2 * slots;
+    L.sumCR += 2 * (int64_t)slots * D;
     L.sumR += (n_rects + 3) & ~3;  // whole 64-byte quads per instance
     L.sumGE += n_gedges;
     L.sumCP += n_cpolys;
@@ -244,6 +253,8 @@ Layout plan_layout(const sepso_map* maps, const sepso_swarm* sw, int n, std::vec
   L.PQ = take(4 * L.sumP);
   L.edges = take(sizeof(EdgeRec) * L.sumGE);
   L.cpolys = take(sizeof(CPoly) * L.sumCP);
+  L.cand = take(16 * L.sumC);
+  L.candr = take(4 * L.sumCR);
   L.rects = take(32 * L.sumR);  // boxes, then centres and half sides
   L.pkind = take(8 * L.sumPoly);
   L.verts = take(8 * L.sumE);
@@ -512,6 +523,8 @@ sepso_status create_batch(const sepso_map* maps, const sepso_swarm* sw, int n, v
   pl.cpolys = at<CPoly>(b, L.cpolys);
   pl.rects = at<float4>(b, L.rects);
   pl.rect_c = pl.rects + L.sumR;
+  pl.cand = at<Cand>(b, L.cand);
+  pl.cand_rows = at<float>(b, L.candr);
   pl.pkind = at<int2>(b, L.pkind);
   pl.verts = at<float2>(b, L.verts);
   pl.poly_ptr = at<int32_t>(b, L.pptr);
@@ -702,6 +715,24 @@ bool frame_plan(const sepso_batch* b, FrameLaunch* f) {
   return 1.05 * std::max(longest, wg) < 11.0 + launches;
 }
 
+// Whether a frame's iterations take one launch each, every block finding its
+// groups' bests from all blocks' candidates at its start, instead of two: a
+// launch less of latency against a second round of memory reads in every
+// block.  It pays while blocks are few (one planner of 8 x 170 particles, 136
+// blocks: 435-545 -> 390-500 us a frame; 8 x 4096, 781 blocks: 2% faster; 64
+// instances, 1088 blocks: even) and a thread has few candidates to look at (10
+// each, 323 blocks of 64 threads: 11% slower; 7 each: 3% faster).
+bool one_launch_plan(const sepso_batch* b) {
+  if (b->buckets.size() != 1 || b->buckets[0].tune.seg_per_thread > 12) return false;
+  const TileBucket& bk = b->buckets[0];
+  const int B = bk.tune.block_threads;
+  // the bests' static LDS comes on top
+  if (iter_lds_bytes(bk.pl, B) + 2048 > 65536 || bk.n_blocks > 4 * kCUs) return false;
+  for (const InstDesc& d : b->desc)
+    if (d.n_blocks + d.G > d.slots || d.n_blocks * bk.pl.ngb_max > 8 * B) return false;
+  return true;
+}
+
 // Enqueue one whole frame of every instance; the first error of the
 // enqueued work (launch errors included).
 hipError_t enqueue_frame(sepso_batch* b, bool move) {
@@ -715,6 +746,16 @@ hipError_t enqueue_frame(sepso_batch* b, bool move) {
   if (frame_plan(b, &fl)) {
     const TileBucket& bk = b->buckets[0];
     if (!launch_frame(bk.pl, bk.tune.seg_per_thread, fl, b->n, tmax, b->stream)) e = hipErrorInvalidValue;
+  } else if (one_launch_plan(b)) {
+    // the last launch finds the bests of iteration tmax and ends the frame
+    const TileBucket& bk = b->buckets[0];
+    for (int k = 0; k <= tmax && e == hipSuccess; ++k) {
+      if (!launch_one(bk.pl, bk.tune.seg_per_thread, bk.n_blocks, bk.tune.block_threads, k, b->stream))
+        e = hipErrorInvalidValue;
+      if (std::any_of(b->desc.begin(), b->desc.end(),
+                      [&](const InstDesc& d) { return d.hsef_every > 0 && (k + 1) % d.hsef_every == 0; }))
+        launch_hsef_one(bk.pl, k, b->stream);
+    }
   } else {
     for (int k = 0; k < tmax && e == hipSuccess; ++k)
       e = enqueue_iteration(b, STEP_FIT | STEP_FRAME, true);

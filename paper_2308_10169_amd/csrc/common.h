@@ -12,6 +12,9 @@ constexpr int kMaxG = 64;        // groups per instance
 constexpr int kHist = 64;        // Auto-Truncation history ring
 constexpr int kStageFloats = 2048;  // general-polygon edge records staged in LDS per pass (256)
 
+constexpr int kCandSlots = 1024;  // most (block, group) pairs of an instance in one-launch iterations
+constexpr int kCandInsts = 64;    // most instances that reserve them
+
 // Learned initializer: 64 x 64 occupancy raster + start/target (4 values)
 // -> 3 x 512 hidden -> 8 groups x 20 waypoints x 2 coordinates.
 constexpr int kRaster = 64;
@@ -88,6 +91,8 @@ struct InstDesc {
   int32_t go;            // group pools: G (gbest_n/f, outer Pbest fitness), G*6 hyper, G*3 outer
   int32_t gpo;           // gbest positions: G*2W
   int32_t dpo;           // per-instance path pools (Tbest, previous plan): 2W
+  int32_t co, slots;     // candidates of one-launch iterations: offset of the entries, slots reserved (0: none)
+  int64_t cro;           // offset of their rows
 };
 
 // Mutable per-instance control block (device resident).
@@ -114,6 +119,12 @@ struct InstCtl {
 
 namespace sepso {
 
+// One-launch iterations: a (block, group) pair's best, one of 2 (n_blocks + G)
+// entries of an instance (even launches' first).  Pair (b, g) has slot b + g.
+//   x: fitness (float bits); y: index in the group, times two, plus which of
+//   two buffers holds its row; z: crossings; w: length (float bits)
+typedef int Cand __attribute__((ext_vector_type(4)));
+
 // Device pointers of every pool in the workspace (passed by value).
 struct Pools {
   int32_t n_inst;
@@ -132,6 +143,8 @@ struct Pools {
   EdgeRec* edges;    // general polygons' edges
   CPoly* cpolys;     // convex polygons
   float4* rects;     // axis-aligned rectangles (x0, y0, x1, y1), x0 < x1, y0 < y1
+  Cand* cand;        // one-launch iterations: the blocks' bests (kernels.hip)
+  float* cand_rows;  // their rows, two buffers
   float4* rect_c;    // their centres and half sides (xc, yc, w/2, h/2)
   int2* pkind;       // per polygon: (1 = rectangle / 2, 3 = convex, counter-clockwise or not / 0 = general, slot in its pool)
   float2* verts;

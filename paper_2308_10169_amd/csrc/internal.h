@@ -31,7 +31,8 @@ struct Layout {
   int64_t sumPD = 0, sumP = 0, sumTilesMax = 0;
   int64_t sumE = 0, sumPP = 0, sumPoly = 0, sumG = 0, sumGD = 0, sumD = 0, initBlocks = 0;
   int64_t sumR = 0, sumGE = 0, sumCP = 0;  // rectangles, edges of other polygons, convex polygons
-  size_t rects = 0, pkind = 0, cpolys = 0;
+  int64_t sumC = 0, sumCR = 0;           // candidates of one-launch iterations, floats of their rows
+  size_t rects = 0, pkind = 0, cpolys = 0, cand = 0, candr = 0;
 };
 
 }  // namespace sepso

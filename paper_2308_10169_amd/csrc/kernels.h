@@ -14,9 +14,14 @@ bool step_supported(int K);
 // 32-bit words of dynamic LDS the fused iteration takes per block.
 size_t iter_lds_words(int pos_floats, int stage_floats, int gb_floats, int ngb_max, int ppb_max,
                       int threads);
+size_t iter_lds_bytes(const Pools& pl, int threads);
 // One iteration's tile kernel (fused, or the update alone without
 // STEP_FIT) over n_blocks entries of pl.blk_tiles; false for an unsupported K.
 bool launch_tiles(const Pools& pl, int K, int n_blocks, int threads, int flags, hipStream_t s);
+// Launch `it` (0 ..) of a frame whose iterations find the bests at their start; false for a K it is not built for.
+bool launch_one(const Pools& pl, int K, int n_blocks, int threads, int it, hipStream_t s);
+// Between launches `it` and it + 1 of such a frame, where an online outer step may be due.
+void launch_hsef_one(const Pools& pl, int it, hipStream_t s);
 // All iterations (at most iters) of the current frame of every instance, one
 // workgroup each; false for a K it is not built for.
 struct FrameLaunch {

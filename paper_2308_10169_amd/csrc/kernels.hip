@@ -10,6 +10,9 @@
 //   update_kernel -- the pending update alone (end of a stepping call);
 //   reduce_kernel -- per instance: group and total bests, Auto Truncation,
 //                    the online self-evolution step, control advance;
+//   iter_one_kernel, hsef_one_kernel -- the same iteration with the bests and
+//                    Auto Truncation found by every block at the next one's
+//                    start, and the self-evolution step (frames of few blocks);
 //   frame_kernel  -- all iterations of a frame of a small instance, one
 //                    workgroup each;
 //   evolve_*      -- the evolution phase's higher level (H-SEPSO).
@@ -510,6 +513,11 @@ __global__ __launch_bounds__(512) void reduce_kernel(Pools pl, int flags) {
 }
 
 
+// Fitness and index as one word that orders by fitness, then by index.
+__device__ __forceinline__ uint64_t best_key(float f, int n) {
+  return (uint64_t)((uint32_t)float_key(f + 0.f) ^ 0x80000000u) << 32 | (uint32_t)n;
+}
+
 // Direct global -> LDS loads (no registers on the way): lane i of the wave
 // writes its word at dst_wave + i, dst_wave the same for the whole wave.
 __device__ __forceinline__ void lds_dma16(const void* src, void* dst_wave) {
@@ -809,8 +817,63 @@ __device__ __forceinline__ void crossings(const Pools& pl, const InstDesc& d, fl
 //  D. per-particle Q and L summed in chunk order (deterministic), fitness
 //     and Pbest; improved particles' positions go from LDS to P.
 // ---------------------------------------------------------------------------
-template <int K, int R, bool FIT>
-__device__ __forceinline__ void iteration(const Pools& pl, int flags) {
+// Group of the e-th of per pairs a block may have, its slot in *slot; -1
+// past the block's groups (the slot is then the instance's first).
+__device__ __forceinline__ int cand_group(const InstDesc& d, int per, int e, int* slot) {
+  const int b = e / per, g = b * d.ppb / d.N + (e - b * per);
+  const bool in = b < d.n_blocks && g <= (min((b + 1) * d.ppb, d.G * d.N) - 1) / d.N;
+  *slot = in ? b + g : 0;
+  return in ? g : -1;
+}
+__device__ __forceinline__ void cand_min(uint64_t* s_best, int g, Cand c) {
+  if (g >= 0) atomicMin(reinterpret_cast<unsigned long long*>(s_best + g), best_key(__int_as_float(c.x), c.y));
+}
+// Block's slot of group g's best, from its word.
+__device__ __forceinline__ int cand_slot(const InstDesc& d, uint64_t best, int g) {
+  return (g * d.N + (int)((uint32_t)best >> 1)) / d.ppb + g;
+}
+// The total best's group: lowest fitness, lowest group on ties.
+__device__ __forceinline__ int cand_total(const uint64_t* s_best, int G) {
+  int tg = 0;
+  for (int g = 1; g < G; ++g)
+    if ((s_best[g] >> 32) < (s_best[tg] >> 32)) tg = g;
+  return tg;
+}
+
+// The online outer step after iteration it + 1 of a one-launch frame, where
+// it is due and the frame does not end: one block per instance.
+__global__ __launch_bounds__(256) void hsef_one_kernel(Pools pl, int it) {
+  __shared__ uint64_t s_best[kMaxG];
+  __shared__ float s_gf[kMaxG], s_hist[kHist];
+  __shared__ int s_stop;
+  const int inst = blockIdx.x, t = threadIdx.x, k = it + 1;
+  const InstDesc d = pl.desc[inst];
+  InstCtl* ctl = pl.ctl + inst;
+  if (ctl->done || d.hsef_every <= 0 || k % d.hsef_every != 0) return;
+  const Cand* ent = pl.cand + d.co + (it & 1) * (d.n_blocks + d.G);
+  for (int g = t; g < d.G; g += blockDim.x) s_best[g] = ~0ull;
+  if (t < kHist) s_hist[t] = ctl->hist[t];
+  __syncthreads();
+  const int per = pl.ngb_max;
+  for (int e = t; e < d.n_blocks * per; e += blockDim.x) {
+    int slot;
+    const int g = cand_group(d, per, e, &slot);
+    cand_min(s_best, g, ent[slot]);
+  }
+  __syncthreads();
+  for (int g = t; g < d.G; g += blockDim.x) s_gf[g] = __int_as_float(ent[cand_slot(d, s_best[g], g)].x);
+  if (t == 0) {
+    const int tg = cand_total(s_best, d.G);
+    const Cand c = ent[cand_slot(d, s_best[tg], tg)];
+    s_hist[it % kHist] = __int_as_float(c.x);
+    s_stop = at_fires(s_hist, k, d.at_mode, d.at_window, d.at_delta, c.z) || k >= d.T;
+  }
+  __syncthreads();
+  if (!s_stop) hsef_step(pl, d, ctl, s_gf);
+}
+
+template <int K, int R, bool FIT, bool ONE = false>
+__device__ __forceinline__ void iteration(const Pools& pl, int flags, int it = 0) {
   // dynamic LDS: positions | obstacle records | Tbest and the gbest rows of
   // the block's groups | an 8-word record per particle (Pbest flags in phase
   // D) | per group w, V_limit / 2, C1..C3 | per-thread crossings (the old
@@ -830,12 +893,41 @@ __device__ __forceinline__ void iteration(const Pools& pl, int flags) {
   const InstDesc d = pl.desc[inst];  // by value: stores cannot make it reload
   InstCtl* ctl = pl.ctl + inst;
   if ((flags & STEP_FRAME) && ctl->done) return;
-  const int k = ctl->k, pending = ctl->pending;
-  const uint32_t ctr = ctl->ctr;
+  // ONE: the frame's launch `it` finds k = it and, from the second on, a move
+  // owed; the control block keeps the frame's first counter until it ends
+  const int k = ONE ? it : ctl->k, pending = ONE ? it > 0 : ctl->pending;
+  const uint32_t ctr = ctl->ctr + (ONE && it > 0 ? (uint32_t)(it - 1) : 0u);
   const int N = d.N, W = d.W, D = 2 * W, S = W + 2;
   const int np = min(d.ppb, d.G * N - p0);  // particles in this block
   const int t = threadIdx.x, B = blockDim.x;
   const float4 ends = pl.ends[inst];  // read before the block's first store
+
+  // ---- bests of the last iteration (ONE) ---------------------------------------
+  // Every block finds its groups' and the total best itself, from all blocks'
+  // candidates.  What that takes from memory comes first of all, in one round
+  // with the rows below; the bests' rows take a second.
+  __shared__ uint64_t s_best[ONE ? kMaxG : 1], s_cand[ONE ? kMaxG : 1];
+  __shared__ float s_hist[ONE ? kHist : 1];
+  __shared__ int s_stop[2];
+  const int b_own = ONE ? p0 / d.ppb : 0, n_slots = d.n_blocks + d.G, per = pl.ngb_max;
+  Cand* ent_now = ONE ? pl.cand + d.co + (it & 1) * n_slots : nullptr;
+  const Cand* ent_last = ONE ? pl.cand + d.co + ((it & 1) ^ 1) * n_slots : nullptr;
+  float* cand_rows = ONE ? pl.cand_rows + d.cro : nullptr;
+  Cand own_last = {0, 0, 0, 0}, c0 = own_last, c1 = own_last;
+  int cg0 = -1, cg1 = -1;
+  float hv = 0.f;
+  if (ONE) {
+    for (int g = t; g < d.G; g += B) s_best[g] = s_cand[g] = ~0ull;
+    __syncthreads();
+    if (pending) {
+      int slot0, slot1;
+      cg0 = cand_group(d, per, t, &slot0);
+      cg1 = cand_group(d, per, t + B, &slot1);
+      c0 = ent_last[slot0];
+      c1 = ent_last[slot1];
+      hv = ctl->hist[t & (kHist - 1)];
+    }
+  }
 
   // ---- A0. the block's global reads ------------------------------------------
   // The block's range starts 16-byte aligned (even particles per block) and
@@ -883,7 +975,45 @@ __device__ __forceinline__ void iteration(const Pools& pl, int flags) {
   const bool has_p = pending && t < np, has_g = pending && t < ngb;
   const int gp = (p0 + t) / N;  // the thread's particle's group
   float hpv[6], hgv[6];
-  if (pending) {
+  if (ONE && pending) {
+    own_last = ent_last[t < ngb ? b_own + g_lo + t : 0];
+    const float* hp = pl.hyper + (d.go + (has_p ? gp : 0)) * 6;
+    const float* hg = pl.hyper + (d.go + g_lo + (has_g ? t : 0)) * 6;
+#pragma unroll
+    for (int i = 0; i < 6; ++i) hpv[i] = hp[i];
+#pragma unroll
+    for (int i = 0; i < 6; ++i) hgv[i] = hg[i];
+  }
+  auto row_of = [&](int g) {
+    return cand_rows + (((uint32_t)s_best[g] & 1u ? n_slots : 0) + cand_slot(d, s_best[g], g)) * (int64_t)D;
+  };
+  int tg = 0;  // ONE: the total best's group and entry
+  Cand tb = {0, 0, 0, 0};
+  if (ONE && pending) {
+    cand_min(s_best, cg0, c0);
+    cand_min(s_best, cg1, c1);
+    for (int e = t + 2 * B; e < d.n_blocks * per; e += B) {
+      int slot;
+      const int g = cand_group(d, per, e, &slot);
+      cand_min(s_best, g, ent_last[slot]);
+    }
+    if (t < kHist) s_hist[t] = hv;
+    __syncthreads();
+    tg = cand_total(s_best, d.G);
+    tb = ent_last[cand_slot(d, s_best[tg], tg)];
+    for (int q = t; q < (ngb + 1) * D; q += B) {
+      const int j = q / D;
+      s_gb[q] = row_of(j == 0 ? tg : g_lo + j - 1)[q - j * D];
+    }
+    if (t == 0) {
+      s_hist[(k - 1) % kHist] = __int_as_float(tb.x);
+      const bool a = at_fires(s_hist, k, d.at_mode, d.at_window, d.at_delta, tb.z);
+      s_stop[0] = a || k >= d.T;
+      s_stop[1] = a;
+      if (b_own == 0) ctl->hist[(k - 1) % kHist] = __int_as_float(tb.x);
+    }
+  }
+  if (!ONE && pending) {
     // Tbest row, then the gbest rows g_lo..g_hi (contiguous in the pool)
     const float* src_t = pl.tbest_pos + d.dpo;
     const float* src_g = pl.gbest_pos + d.gpo + g_lo * D;
@@ -925,6 +1055,39 @@ __device__ __forceinline__ void iteration(const Pools& pl, int flags) {
     for (int gl = t + B; gl < ngb; gl += B) put_group(gl, pl.hyper + (d.go + g_lo + gl) * 6);
   }
   __syncthreads();
+  if (ONE && pending && s_stop[0]) {  // the frame ends with iteration k's bests: its first block writes them
+    if (b_own == 0) {
+      for (int q = t; q < d.G * D; q += B) {
+        const int g = q / D, dd = q - g * D;
+        const float x = row_of(g)[dd];
+        pl.gbest_pos[d.gpo + q] = x;
+        if (g == tg) pl.tbest_pos[d.dpo + dd] = pl.prev_path[d.dpo + dd] = x;
+      }
+      for (int g = t; g < d.G; g += B) {
+        const Cand c = ent_last[cand_slot(d, s_best[g], g)];
+        pl.gbest_n[d.go + g] = c.y >> 1;
+        pl.gbest_f[d.go + g] = __int_as_float(c.x);
+      }
+      if (t == 0) {
+        ctl->k = k;
+        ctl->pending = 0;
+        ctl->ctr = ctr + 1u;
+        ctl->tb_g = tg;
+        ctl->tb_n = tb.y >> 1;
+        ctl->tb_f = __int_as_float(tb.x);
+        ctl->truncated = s_stop[1];
+        ctl->res_cost = __int_as_float(tb.x);
+        ctl->res_len = __int_as_float(tb.w);
+        ctl->res_q = tb.z;
+        ctl->res_iters = k;
+        ctl->res_trunc = s_stop[1];
+        ctl->have_prev = 1;
+        ctl->frame += 1;
+        ctl->done = 1;
+      }
+    }
+    return;
+  }
 
   // ---- A2. update ---------------------------------------------------------------
   // The element loop walks (particle, coordinate) incrementally, without
@@ -1056,10 +1219,10 @@ __device__ __forceinline__ void iteration(const Pools& pl, int flags) {
   s_q[t] = ct;
   s_l[t] = len_sum;
   __syncthreads();
+  float pf_new = INFINITY, L = 0.f;  // of particle t
+  int q = 0, imp = 0;
   if (t < np) {
     const int j = t;
-    int q = 0;
-    float L = 0.f;
     for (int cc = 0; cc < C; ++cc) {  // chunk order: deterministic
       for (int r = 0; r < R; ++r) q += s_q[r * BR + j + cc * d.ppb];
       L += s_l[j + cc * d.ppb];  // lengths from group 0 only
@@ -1073,15 +1236,39 @@ __device__ __forceinline__ void iteration(const Pools& pl, int flags) {
     pl.L[po] = L;
     pl.Q[po] = q;
     const float fc = isfinite(fv) ? fv : INFINITY;
-    const int imp = fc < pf_old;
+    imp = fc < pf_old;
     if (imp) {
       pl.Pf[po] = fc;
       pl.PL[po] = L;
       pl.PQ[po] = q;
     }
     s_imp[j] = imp;
+    pf_new = imp ? fc : pf_old;
+    if (ONE)
+      atomicMin(reinterpret_cast<unsigned long long*>(s_cand + gp - g_lo), best_key(pf_new, p0 + t - gp * N));
   }
   __syncthreads();
+  if (ONE) {
+    // The block's best of each of its groups joins the next launch's
+    // candidates: one that has just improved with its row, into the buffer
+    // that the last launch's does not name; otherwise it is the last launch's.
+    // (Before the first move every particle's row is its Pbest row.)
+    const bool fresh = imp || it == 0;
+    int* s_src = s_q;  // per group: the particle whose row is new, or -1 (the crossings are dead by then)
+    if (t < np && (int)(uint32_t)s_cand[gp - g_lo] == p0 + t - gp * N) s_src[gp - g_lo] = fresh ? t : -1;
+    __syncthreads();
+    for (int gl = 0; gl < ngb; ++gl) {
+      const int j = s_src[gl], slot = b_own + g_lo + gl;
+      if (j >= 0) {
+        const int buf = it == 0 ? 0 : ~ent_last[slot].y & 1;
+        float* row = cand_rows + (buf * n_slots + slot) * (int64_t)D;
+        for (int e = t; e < D; e += B) row[e] = s_buf[j * D + e];
+        if (t == j) ent_now[slot] = Cand{__float_as_int(pf_new), 2 * (p0 + t - gp * N) + buf, q, __float_as_int(L)};
+      } else if (t == gl) {
+        ent_now[slot] = own_last;
+      }
+    }
+  }
   // Improved particles' rows go to P from the LDS copy of the new positions,
   // by the same float4 walk as phase A.
   {
@@ -1124,6 +1311,15 @@ template <int K>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(K <= 8 ? 6 : 1))) void
 iter_kernel(Pools pl, int flags) {
   iteration<K, 1, true>(pl, flags);
+}
+// A frame's launch `it` with the bests' step at its start (see ONE above): a
+// chain of latencies, so one launch with a second round of reads takes the
+// place of two launches (8 x 170 particles, 20 waypoints, 30 rectangles: 10.9
+// -> 9.6 us per iteration; 8 x 4096, 64 waypoints, 600 obstacles: 243 -> 236).
+// Held to six waves per SIMD the K = 8 form spills, so it is left at five.
+template <int K, int R>
+__global__ __launch_bounds__(256) void iter_one_kernel(Pools pl, int it) {
+  iteration<K, R, true, true>(pl, STEP_FIT | STEP_FRAME, it);
 }
 template <int K, int R>
 __global__ __launch_bounds__(256) void iter_kernel_split(Pools pl, int flags) {
@@ -1503,6 +1699,26 @@ static void launch_tiles_k(const Pools& pl, int n_blocks, int threads, int flags
     hipLaunchKernelGGL(update_kernel<K>, dim3(n_blocks), dim3(threads), lds, s, pl, flags);
 }
 
+template <int K>
+static void launch_one_k(const Pools& pl, int n_blocks, int threads, int it, hipStream_t s) {
+  const size_t lds = iter_lds_bytes(pl, threads);
+  if (pl.rsplit == 4)
+    hipLaunchKernelGGL((iter_one_kernel<K, 4>), dim3(n_blocks), dim3(threads), lds, s, pl, it);
+  else if (pl.rsplit == 2)
+    hipLaunchKernelGGL((iter_one_kernel<K, 2>), dim3(n_blocks), dim3(threads), lds, s, pl, it);
+  else
+    hipLaunchKernelGGL((iter_one_kernel<K, 1>), dim3(n_blocks), dim3(threads), lds, s, pl, it);
+}
+
+bool launch_one(const Pools& pl, int K, int n_blocks, int threads, int it, hipStream_t s) {
+  switch (K) {
+    case 4: launch_one_k<4>(pl, n_blocks, threads, it, s); return true;
+    case 8: launch_one_k<8>(pl, n_blocks, threads, it, s); return true;
+    case 12: launch_one_k<12>(pl, n_blocks, threads, it, s); return true;
+    default: return false;
+  }
+}
+
 bool launch_tiles(const Pools& pl, int K, int n_blocks, int threads, int flags, hipStream_t s) {
   if (n_blocks <= 0) return true;
   switch (K) {
@@ -1513,6 +1729,10 @@ bool launch_tiles(const Pools& pl, int K, int n_blocks, int threads, int flags, 
     case 24: launch_tiles_k<24>(pl, n_blocks, threads, flags, s); return true;
     default: return false;
   }
+}
+
+void launch_hsef_one(const Pools& pl, int it, hipStream_t s) {
+  hipLaunchKernelGGL(hsef_one_kernel, dim3(pl.n_inst), dim3(256), 0, s, pl, it);
 }
 
 size_t frame_lds_bytes(int G, int N, int W, int threads, int ahead) {
