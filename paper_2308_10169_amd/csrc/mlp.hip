@@ -22,7 +22,9 @@ __device__ __forceinline__ float from_bf16(uint16_t h) { return __uint_as_float(
 // ---------------------------------------------------------------------------
 // Input features of instance i (row i of X): 64 x 64 occupancy (cell centre
 // inside any obstacle polygon, even-odd rule) followed by start and target
-// normalised by the map size; zero padding up to kLinInPad.
+// normalised by the map size; zero padding up to kLinInPad.  An edge is read
+// once for a thread's sixteen cells (once per cell it was a chain of scalar
+// loads): 256 instances of 4 rectangles 39 -> 14 us.
 // ---------------------------------------------------------------------------
 __global__ __launch_bounds__(256) void raster_kernel(Pools pl, uint16_t* X, int ldx,
                                                      int32_t* eligible) {
@@ -31,24 +33,30 @@ __global__ __launch_bounds__(256) void raster_kernel(Pools pl, uint16_t* X, int 
   const float2* verts = pl.verts + d.eo;
   const int32_t* pp = pl.poly_ptr + d.plo;
   uint16_t* row = X + (int64_t)inst * ldx;
-  for (int cell = threadIdx.x; cell < kRaster * kRaster; cell += blockDim.x) {
-    const int r = cell / kRaster, c = cell - r * kRaster;
-    const float px = (c + 0.5f) * d.width / kRaster, py = (r + 0.5f) * d.height / kRaster;
-    int inside = 0;
-    for (int q = 0; q < d.n_polys && !inside; ++q) {
-      const int v0 = pp[q], m = pp[q + 1] - v0;
-      int odd = 0;
-      for (int j = 0; j < m; ++j) {
-        const float2 a = verts[v0 + j], b = verts[v0 + (j + 1 == m ? 0 : j + 1)];
-        if ((a.y > py) != (b.y > py)) {
+  // a thread's cells are one column's, every fourth row: bit i of a word is
+  // row r0 + 4 i
+  constexpr int kCells = kRaster * kRaster / 256;
+  const int c = threadIdx.x % kRaster, r0 = threadIdx.x / kRaster;
+  const float px = (c + 0.5f) * d.width / kRaster;
+  uint32_t inside = 0;
+  for (int q = 0; q < d.n_polys; ++q) {
+    const int v0 = pp[q], m = pp[q + 1] - v0;
+    uint32_t odd = 0;
+    for (int j = 0; j < m; ++j) {
+      const float2 a = verts[v0 + j], b = verts[v0 + (j + 1 == m ? 0 : j + 1)];
+#pragma unroll
+      for (int i = 0; i < kCells; ++i) {
+        const float py = (r0 + 4 * i + 0.5f) * d.height / kRaster;
+        if ((a.y > py) != (b.y > py)) {  // the same for a whole wave
           const float xc = a.x + (py - a.y) * (b.x - a.x) / (b.y - a.y);
-          if (px < xc) odd ^= 1;
+          if (px < xc) odd ^= 1u << i;
         }
       }
-      inside = odd;
     }
-    row[cell] = inside ? 0x3F80 : 0;  // 1.0 or 0.0
+    inside |= odd;
   }
+#pragma unroll
+  for (int i = 0; i < kCells; ++i) row[(r0 + 4 * i) * kRaster + c] = inside >> i & 1 ? 0x3F80 : 0;  // 1.0 or 0.0
   if (threadIdx.x < kLinInPad - kRaster * kRaster) {
     const int j = threadIdx.x;
     const float4 e = pl.ends[inst];
