@@ -239,38 +239,59 @@ __global__ __launch_bounds__(256) void bf_iter_kernel(BFDev s) {
   }
 }
 
-__global__ __launch_bounds__(256) void bf_reduce_kernel(BFDev s, int fit) {
-  __shared__ float s_f[256];
-  __shared__ int s_n[256];
-  const int g = blockIdx.x, t = threadIdx.x, N = s.N;
+// A chain of latencies between two large launches: 1024 threads, so that a
+// group's Pbest scan is one round of loads (2048 particles: two per thread),
+// the waves' bests by shuffles and one barrier.  16384 x 1000: 6.6 -> 4.7 us
+// (256 threads, a tree of eight barriers).
+__global__ __launch_bounds__(1024) void bf_reduce_kernel(BFDev s, int fit) {
+  __shared__ float s_f[16];
+  __shared__ int s_n[16];
+  const int g = blockIdx.x, t = threadIdx.x, N = s.N, nw = blockDim.x >> 6;
+  auto better = [](float fa, int na, float fb, int nb) { return fa < fb || (fa == fb && na < nb); };
   if (fit) {
     float bf = INFINITY;
     int bn = 0x7fffffff;
-    for (int n = t; n < N; n += blockDim.x) {
-      const float f = s.Pf[g * N + n];
-      if (f < bf || (f == bf && n < bn)) {
-        bf = f;
-        bn = n;
+    const float* Pf = s.Pf + (int64_t)g * N;
+    for (int n0 = t; n0 < N; n0 += 4 * blockDim.x) {  // four loads in flight
+      float f[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int n = n0 + u * (int)blockDim.x;
+        f[u] = Pf[n < N ? n : n0];
       }
-    }
-    s_f[t] = bf;
-    s_n[t] = bn;
-    __syncthreads();
-    for (int m = blockDim.x / 2; m > 0; m >>= 1) {
-      if (t < m) {
-        const float of = s_f[t + m];
-        const int on = s_n[t + m];
-        if (of < s_f[t] || (of == s_f[t] && on < s_n[t])) {
-          s_f[t] = of;
-          s_n[t] = on;
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int n = n0 + u * (int)blockDim.x;
+        if (n < N && better(f[u], n, bf, bn)) {
+          bf = f[u];
+          bn = n;
         }
       }
-      __syncthreads();
     }
-    const int n = s_n[0] < N ? s_n[0] : 0;
+    auto across = [&](int m) {
+      const float of = __shfl_xor(bf, m);
+      const int on = __shfl_xor(bn, m);
+      if (better(of, on, bf, bn)) {
+        bf = of;
+        bn = on;
+      }
+    };
+#pragma unroll
+    for (int m = 32; m > 0; m >>= 1) across(m);
+    if ((t & 63) == 0) {
+      s_f[t >> 6] = bf;
+      s_n[t >> 6] = bn;
+    }
+    __syncthreads();
+    const int l = t & 15;
+    bf = l < nw ? s_f[l] : INFINITY;
+    bn = l < nw ? s_n[l] : 0x7fffffff;
+#pragma unroll
+    for (int m = 8; m > 0; m >>= 1) across(m);
+    const int n = bn < N ? bn : 0;
     if (t == 0) {
       s.gbest_n[g] = n;
-      s.gbest_f[g] = s_f[0];
+      s.gbest_f[g] = bf;
     }
     const float4* src = reinterpret_cast<const float4*>(s.P + ((int64_t)g * N + n) * s.Dp);
     float4* dst = reinterpret_cast<float4*>(s.gbest_pos + (int64_t)g * s.Dp);
@@ -665,7 +686,7 @@ void launch_bf_step(const BFDev& s, bool fit, hipStream_t st) {
     case BF_RASTRIGIN: launch_bf_iter<BF_RASTRIGIN>(s, fit, st); break;
     default: launch_bf_iter<BF_GRIEWANK>(s, fit, st); break;
   }
-  hipLaunchKernelGGL(bf_reduce_kernel, dim3(s.G), dim3(256), 0, st, s, fit ? 1 : 0);
+  hipLaunchKernelGGL(bf_reduce_kernel, dim3(s.G), dim3(s.N > 512 ? 1024 : 256), 0, st, s, fit ? 1 : 0);
 }
 
 }  // namespace sepso
