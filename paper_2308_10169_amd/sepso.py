@@ -51,6 +51,9 @@ class CFrameResult(C.Structure):
                 ("device_ms", C.c_float)]
 
 
+_RESULT_DTYPE = np.dtype(CFrameResult)
+
+
 class CState(C.Structure):
     _fields_ = [("X", fp), ("V", fp), ("P", fp), ("f", fp), ("L", fp), ("Pf", fp), ("PL", fp),
                 ("Q", ip), ("PQ", ip), ("gbest_n", ip), ("gbest_f", fp), ("hyper", fp),
@@ -437,6 +440,7 @@ class BatchPlanner:
         off = (C.c_int64 * (n + 1))()
         _check(L.sepso_batch_path_offsets(h, off))
         self.path_off = np.array(off[:], dtype=np.int64)
+        self._path_slices = [slice(off[i], off[i + 1]) for i in range(n)]
 
     def close(self):
         if self.h:
@@ -454,13 +458,14 @@ class BatchPlanner:
         paths = np.zeros(max(int(self.path_off[-1]), 1), np.float32) if want_paths else None
         _check(_lib.sepso_batch_plan(self.h, int(n_frames), res,
                                      paths.ctypes.data_as(fp) if want_paths else None))
-        cost = np.array([r.cost for r in res], np.float64).reshape(n_frames, self.n)
-        iters = np.array([r.iters for r in res], np.int32).reshape(n_frames, self.n)
-        q = np.array([r.crossings for r in res], np.int32).reshape(n_frames, self.n)
-        trunc = np.array([r.truncated for r in res], np.int32).reshape(n_frames, self.n)
+        # fields through one view of the results (an attribute read per field
+        # and instance took 0.4 ms of a 1024-instance frame's 13.4)
+        r = np.frombuffer(res, dtype=_RESULT_DTYPE).reshape(n_frames, self.n)
+        cost, iters = r["cost"].astype(np.float64), r["iters"].astype(np.int32)
+        q, trunc = r["crossings"].astype(np.int32), r["truncated"].astype(np.int32)
         out = dict(cost=cost, iters=iters, crossings=q, truncated=trunc)
         if want_paths:
-            out["paths"] = [paths[self.path_off[i]:self.path_off[i + 1]] for i in range(self.n)]
+            out["paths"] = [paths[s] for s in self._path_slices]
         return out
 
     def get_state(self, i):
