@@ -220,10 +220,11 @@ __global__ __launch_bounds__(64 * kSmallWaves) void gemm_small_kernel(const uint
 // same one).  8192 x 512 x 4128: 73.8 + 7.4 us (two slices added up by a second
 // launch) -> 43 us in a training step, 37 by itself (930 TFLOP/s); 8192 x 512
 // x 512: 17 -> 12 us.
-template <int BM, int BN, int WM, int WN>
+template <int BM, int BN, int WM, int WN, int D = 2>
 __global__ __launch_bounds__(64 * (BM / WM) * (BN / WN)) void gemm_nt_kernel(
     const uint16_t* __restrict__ A, int lda, const uint16_t* __restrict__ B, int ldb, int M, int N, int steps,
     int kper, Epi ep) {
+  static_assert(D >= 2 && 6 % D == 0, "the loop takes six steps");
   constexpr int T = 64 * (BM / WM) * (BN / WN), NI = WM / 16, NJ = WN / 16;
   constexpr int CA = (BM * 8 + T - 1) / T, CB = BN * 8 / T;  // 16-byte chunks per thread and step
   __shared__ __attribute__((aligned(16))) uint16_t s_t[3][(BM + BN) * 64];
@@ -235,7 +236,7 @@ __global__ __launch_bounds__(64 * (BM / WM) * (BN / WN)) void gemm_nt_kernel(
   const int tr = t >> 3, tc = t & 7;  // row (of T / 8 at a time) and chunk this thread carries
   struct Stage {
     u32x4 a[CA], b[CB];
-  } r[2];
+  } r[D];
   auto fetch = [&](Stage& f, int k) {  // k: MFMA step; the second half of a last odd step is not used
     // (past the end: the last stage again, not used)
     const bool whole = k + 1 < steps;
@@ -288,8 +289,9 @@ __global__ __launch_bounds__(64 * (BM / WM) * (BN / WN)) void gemm_nt_kernel(
   for (int c = 0; c < 2; ++c) {
     stash_a(r[c], s_t[c]);
     stash_b(r[c], s_t[c]);
-    fetch(r[c], 4 + 2 * c);
   }
+#pragma unroll
+  for (int c = 0; c < D; ++c) fetch(r[c], 4 + 2 * c);
   __syncthreads();
   auto frag = [&](const uint16_t* s, int row, int h) {
     return *reinterpret_cast<const bf16x8*>(s + row * 64 + (((4 * h + kg) ^ (row & 7)) << 3));
@@ -321,12 +323,12 @@ __global__ __launch_bounds__(64 * (BM / WM) * (BN / WN)) void gemm_nt_kernel(
     read(s1, 0);
     stash_b(f, s2);
     if (k + 1 < steps) product(1);
-    fetch(f, k + 8);
+    fetch(f, k + 4 + 2 * D);
   };
   for (int k0 = 0; k0 < steps; k0 += 12) {
 #pragma unroll
     for (int c = 0; c < 6; ++c)
-      step(k0 + 2 * c, s_t[c % 3], s_t[(c + 1) % 3], s_t[(c + 2) % 3], r[c & 1]);
+      step(k0 + 2 * c, s_t[c % 3], s_t[(c + 1) % 3], s_t[(c + 2) % 3], r[c % D]);
   }
   if (left < kper) end_slice();
   apply_epi<NI, NJ>(ep, M, N, m0 + wm + r16, n0 + wn + kg * 4, tot);
@@ -721,18 +723,20 @@ void launch_gemm(const uint16_t* A, int lda, const uint16_t* B, int ldb, int M, 
   // LDS staging for slices of two steps (K = 512, M = 512 4.4 and 5.7 by 64 x
   // 64; M = 1024 6.1 and 5.8).
   auto tiles = [&](int bm, int bn) { return ((M + bm - 1) / bm) * ((N + bn - 1) / bn); };
-#define NT(BM, BN, WM, WN)                                                                                       \
-  hipLaunchKernelGGL((gemm_nt_kernel<BM, BN, WM, WN>), dim3(tiles(BM, BN)), dim3(64 * (BM / WM) * (BN / WN)), 0, \
+#define NT(BM, BN, WM, WN, D)                                                                                       \
+  hipLaunchKernelGGL((gemm_nt_kernel<BM, BN, WM, WN, D>), dim3(tiles(BM, BN)), dim3(64 * (BM / WM) * (BN / WN)), 0, \
                      s, A, lda, B, ldb, M, N, steps, kper, ep)
   if (tiles(128, 128) >= 160)
-    NT(128, 128, 64, 32);
+    NT(128, 128, 64, 32, 2);
   else if (tiles(64, 128) >= 160)
-    NT(64, 128, 32, 32);
+    NT(64, 128, 32, 32, 2);
   else if (kper <= 2 && S <= kSmallWaves && tiles(32, 32) <= 256)
     hipLaunchKernelGGL(gemm_small_kernel, dim3(tiles(32, 32)), dim3(64 * kSmallWaves), 0, s, A, lda, B, ldb, M, N,
                        steps, kper, S, ep);
-  else
-    NT(64, 64, 16, 32);
+  else if (K < 2048)
+    NT(64, 64, 16, 32, 2);
+  else  // few blocks and a long K: the inputs' rows come from HBM, six steps ahead
+    NT(64, 64, 16, 32, 6);
 #undef NT
 }
 
