@@ -1447,7 +1447,10 @@ __global__ __launch_bounds__(kFrameThreads) void frame_kernel(Pools pl, int B, i
             o[1] = u01(r.v[1]);
             o[2] = u01(r.v[2]);
           }
-        if (ahead > 1) __syncthreads();
+        // read by all the particle's parts, mostly in other waves; `ahead` (the
+        // batch's) can be 1 where this instance has several (one part: its own
+        // thread wrote it)
+        if (parts > 1) __syncthreads();
       }
       const float* rr = s_r + 3 * (ahead - drawn) * nP;
       --drawn;
