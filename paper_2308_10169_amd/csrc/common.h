@@ -100,6 +100,7 @@ struct InstCtl {
   int32_t k;             // iterations with bests done in the current plan
   int32_t pending;       // iteration k's velocity/position update not applied yet
   int32_t done;          // the current frame has ended
+  int32_t ended;         // one-launch iterations: the launch that ended it (INT32_MAX while it runs)
   int32_t frame;         // frames planned so far (random stream position for inits)
   uint32_t ctr;          // counter of iteration k's update draws
   uint32_t epoch_ctr;    // outer-swarm steps taken (random stream position)

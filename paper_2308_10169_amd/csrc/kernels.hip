@@ -264,6 +264,7 @@ __global__ __launch_bounds__(256) void init_kernel(Pools pl, int frame_override,
       ctl->k = 0;
       ctl->pending = 0;
       ctl->done = 0;
+      ctl->ended = INT32_MAX;
       ctl->tb_g = 0;
       ctl->tb_n = 0;
       ctl->tb_f = INFINITY;
@@ -892,7 +893,11 @@ __device__ __forceinline__ void iteration(const Pools& pl, int flags, int it = 0
   const int inst = bt.x, p0 = bt.y;
   const InstDesc d = pl.desc[inst];  // by value: stores cannot make it reload
   InstCtl* ctl = pl.ctl + inst;
-  if ((flags & STEP_FRAME) && ctl->done) return;
+  // ONE: the launch that ends a frame has its first block write that while
+  // others start, and every wave reads it by itself.  Only what an earlier
+  // launch wrote may count, or a block would lose some of its waves: so the
+  // word is the launch's number, and before and after the write `it` goes on.
+  if (ONE ? ctl->ended < it : (flags & STEP_FRAME) && ctl->done) return;
   // ONE: the frame's launch `it` finds k = it and, from the second on, a move
   // owed; the control block keeps the frame's first counter until it ends
   const int k = ONE ? it : ctl->k, pending = ONE ? it > 0 : ctl->pending;
@@ -1083,7 +1088,8 @@ __device__ __forceinline__ void iteration(const Pools& pl, int flags, int it = 0
         ctl->res_trunc = s_stop[1];
         ctl->have_prev = 1;
         ctl->frame += 1;
-        ctl->done = 1;
+        ctl->done = 1;  // for the next kernel; this one's blocks go by `ended`
+        ctl->ended = it;
       }
     }
     return;
