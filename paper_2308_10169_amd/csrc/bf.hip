@@ -331,23 +331,31 @@ __global__ __launch_bounds__(256) void bf_best_kernel(BFDev s, float* out) {
 // (bf_move, bf_terms, the same wave butterflies), so the results are
 // bit-identical.  The control word is read here and advanced by bf_ctl_kernel
 // afterwards (every workgroup reads it unchanged).
-constexpr int kBFRunThreads = 1024;
+
+// Particles per lane group past two, and the most threads of a workgroup with R
+// of them.  A lane's registers (128 with 1024 threads) hold three particles'
+// state and one particle's temporaries, or two with Griewank's cosine, which
+// past two takes six on half the threads: its third made the loop spill.
+// 12 x 30 particles of 18: 5.4 -> 5.3 us an iteration with Rastrigin (before:
+// three with spills), Griewank 7.3 -> 7.7; 5 x 8 of 137, Griewank 5.2 -> 7.4.
+constexpr int bf_run_many(int func) { return func == BF_GRIEWANK ? 6 : 3; }
+constexpr int bf_run_threads(int R) { return R <= 3 ? 1024 : 512; }
 constexpr int kBFRunMax = 64 * 1024;  // LDS bytes
 
 struct BFRunPlan {
   int Q, L;          // float4 groups per row, lanes per particle (power of two >= Q)
-  int R, threads;    // particles per thread's lane group, threads of the workgroup
+  int R, threads;    // particles per thread's lane group (1, 2 or bf_run_many), threads of the workgroup
   int ahead;         // iterations whose random factors are drawn together
   size_t bytes;      // dynamic LDS
 };
 
-inline BFRunPlan bf_run_plan(int Gs, int N, int Dp) {
+inline BFRunPlan bf_run_plan(int func, int Gs, int N, int Dp) {
   BFRunPlan r{};
   r.Q = Dp / 4;
   r.L = 1;
   while (r.L < r.Q) r.L *= 2;
   const size_t nS = (size_t)Gs * N;
-  r.R = (int)((nS * r.L + kBFRunThreads - 1) / kBFRunThreads);
+  r.R = nS * r.L <= 1024 ? 1 : nS * r.L <= 2048 ? 2 : bf_run_many(func);
   const size_t per = (nS + r.R - 1) / r.R;
   r.threads = (int)((per * r.L + 63) / 64 * 64);
   for (r.ahead = r.L < 8 ? r.L : 8;; r.ahead /= 2) {
@@ -435,7 +443,7 @@ __device__ __forceinline__ uint64_t min_shfl(uint64_t k, int m) {
 // (1.17 us per iteration; with the state in LDS, five barriers per iteration
 // and one thread scanning each group's Pbest it was 3.6).
 template <int FUNC, int R>
-__global__ __launch_bounds__(kBFRunThreads) void
+__global__ __launch_bounds__(bf_run_threads(R)) void
 bf_run_kernel(BFDev s, int n_fit, int flush, int L, int ahead, int fused) {
   extern __shared__ float4 s_dyn4[];
   const int sw = blockIdx.x, t = threadIdx.x, B = blockDim.x;
@@ -448,6 +456,7 @@ bf_run_kernel(BFDev s, int n_fit, int flush, int L, int ahead, int fused) {
   uint64_t* sB = reinterpret_cast<uint64_t*>(sC + nS * ahead);
   const int lane = t & 63, ls = t & (L - 1), per = B / L;
   const int e = 4 * ls;  // first coordinate of this lane
+  const int lq = ls < Q ? ls : Q - 1;
 
   // particle r * per + t / L of the swarm, for r < R; lanes past a row's end
   // (or the last particle) hold nothing
@@ -481,21 +490,21 @@ bf_run_kernel(BFDev s, int n_fit, int flush, int L, int ahead, int fused) {
   const BFCtl c0 = *s.ctl;
   int k = c0.k, pending = c0.pending;
   uint32_t ctr = c0.ctr;
-  // the bests' rows for a move owed at the start come from memory
-  float4 gb[R], tb = make_float4(0.f, 0.f, 0.f, 0.f);
+  // the particles whose rows the next move takes as the groups' and the total
+  // best; for a move owed at the start the groups' best rows come from memory,
+  // in the places of their first particles, into the copy that step 0 leaves
+  int gbest[R], tbest = 0;
 #pragma unroll
-  for (int r = 0; r < R; ++r) gb[r] = tb;
-  uint64_t best[R];
-#pragma unroll
-  for (int r = 0; r < R; ++r) best[r] = bf_key(INFINITY, grp[r] * N);
-  if (pending && ls < Q) {
-    const float4* G4 = reinterpret_cast<const float4*>(s.gbest_pos) + (int64_t)g0 * Q;
+  for (int r = 0; r < R; ++r) gbest[r] = grp[r] * N;
+  if (pending) {
     int tg = 0;
     for (int g = 1; g < Gs; ++g)
       if (s.gbest_f[g0 + g] < s.gbest_f[g0 + tg]) tg = g;
-    tb = G4[tg * Q + ls];
+    tbest = tg * N;
 #pragma unroll
-    for (int r = 0; r < R; ++r) gb[r] = G4[grp[r] * Q + ls];
+    for (int r = 0; r < R; ++r)
+      if (row[r] && id[r] == gbest[r])
+        sP[(nS + id[r]) * Q + ls] = reinterpret_cast<const float4*>(s.gbest_pos)[(int64_t)(g0 + grp[r]) * Q + ls];
   }
   __syncthreads();
 
@@ -518,18 +527,22 @@ bf_run_kernel(BFDev s, int n_fit, int flush, int L, int ahead, int fused) {
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");  // read by the particle's own lanes
       }
       const int kk = k < s.T ? k : s.T;
+      const float4* last = sP + (step & 1 ? 0 : nS * Q) + lq;
+      const float4 tb = last[tbest * Q];
 #pragma unroll
       for (int r = 0; r < R; ++r) {
+        const float4 gb = last[gbest[r] * Q];
         const float4 c = sC[id[r] * ahead + (ahead - drawn)];
         const float w = h3[r] - hs[r] * (float)kk;
         float* xs = &x4[r].x;
         float* vs = &v4[r].x;
         const float* ps = &p4[r].x;
-        const float* gs = &gb[r].x;
+        const float* gs = &gb.x;
         const float* ts = &tb.x;
 #pragma unroll
         for (int j = 0; j < 4; ++j)  // (past a row's end too: nothing reads those)
           xs[j] = bf_move(xs[j], vs[j], ps[j], gs[j], ts[j], w, c.x, c.y, c.z, vmax[r], s.lo, s.hi);
+        if (R > 2) __builtin_amdgcn_sched_barrier(0);  // one particle's temporaries at a time
       }
       --drawn;
     }
@@ -567,13 +580,14 @@ bf_run_kernel(BFDev s, int n_fit, int flush, int L, int ahead, int fused) {
         // (an infinite or NaN Pbest is no group's best)
         if (own[r] && pf[r] < INFINITY)
           atomicMin(reinterpret_cast<unsigned long long*>(sB + words + grp[r]), bf_key(pf[r], id[r]));
+        if (R > 2) __builtin_amdgcn_sched_barrier(0);
       }
       __syncthreads();
       // total best: lowest fitness, lowest group and index on ties
       const int wl = Gs > 8 ? lane : lane & 7;
       uint64_t tot = sB[words + (wl < Gs ? wl : 0)];
 #pragma unroll
-      for (int r = 0; r < R; ++r) best[r] = sB[words + grp[r]];
+      for (int r = 0; r < R; ++r) gbest[r] = (int)(uint32_t)sB[words + grp[r]];
       tot = min_dpp<0xB1>(tot);   // quad_perm 1,0,3,2
       tot = min_dpp<0x4E>(tot);   // quad_perm 2,3,0,1
       tot = min_dpp<0x141>(tot);  // row_half_mirror
@@ -582,33 +596,31 @@ bf_run_kernel(BFDev s, int n_fit, int flush, int L, int ahead, int fused) {
         tot = min_shfl(tot, 16);
         tot = min_shfl(tot, 32);
       }
-      if (ls < Q) {
-        tb = sP[rows + (int)(uint32_t)tot * Q];
-#pragma unroll
-        for (int r = 0; r < R; ++r) gb[r] = sP[rows + (int)(uint32_t)best[r] * Q];
-      }
+      tbest = (int)(uint32_t)tot;
       k += 1;
     }
     ctr += pending ? 1u : 0u;
     pending = fit ? 1 : 0;
   }
 
+  const int copy = (n_fit - 1) & 1;  // of the last evaluated step, if there is one
 #pragma unroll
   for (int r = 0; r < R; ++r) {
+    asm("" : "+v"(id[r]));  // addresses are made anew, not kept through the loop
     const int64_t q = r0 + (int64_t)id[r] * Q + ls;
     if (row[r]) {
       reinterpret_cast<float4*>(s.X)[q] = x4[r];
       reinterpret_cast<float4*>(s.V)[q] = v4[r];
       reinterpret_cast<float4*>(s.P)[q] = p4[r];
       if (n_fit > 0 && id[r] == grp[r] * N)  // a group's first particle writes its best
-        reinterpret_cast<float4*>(s.gbest_pos)[(int64_t)(g0 + grp[r]) * Q + ls] = gb[r];
+        reinterpret_cast<float4*>(s.gbest_pos)[(int64_t)(g0 + grp[r]) * Q + ls] = sP[(copy * nS + gbest[r]) * Q + ls];
     }
     if (own[r]) {
       s.Pf[(int64_t)g0 * N + id[r]] = pf[r];
       s.f[(int64_t)g0 * N + id[r]] = fv[r];
       if (n_fit > 0 && id[r] == grp[r] * N) {
-        s.gbest_f[g0 + grp[r]] = bf_key_f(best[r]);
-        s.gbest_n[g0 + grp[r]] = (int)(uint32_t)best[r] - grp[r] * N;
+        s.gbest_f[g0 + grp[r]] = bf_key_f(sB[copy * Gs + grp[r]]);
+        s.gbest_n[g0 + grp[r]] = gbest[r] - grp[r] * N;
       }
     }
   }
@@ -630,17 +642,18 @@ __global__ void bf_ctl_kernel(BFDev s, int n_fit, int flush) {
 }
 
 // Rows of at most 256 floats, and Pbest rows (twice) and random factors within
-// 64 KiB of LDS with at most three particles per lane group.  Up to there the
-// one-launch run is the faster path whatever the swarms' number: an iteration
-// costs 0.6-3 us against 8.6 us or more for the two launches.
+// 64 KiB of LDS with at most three particles per lane group of 1024 threads.  Up
+// to there the one-launch run is the faster path whatever the swarms' number: an
+// iteration costs 0.6-7.7 us (2048 swarms of 12 x 30 x 18: 43) against 8.8 (480)
+// or more for the two launches.
 bool bf_run_fits(const BFDev& s) {
-  const BFRunPlan r = bf_run_plan(s.Gs, s.N, s.Dp);
-  return s.Dp <= 256 && r.bytes <= kBFRunMax && r.R <= 3;
+  const BFRunPlan r = bf_run_plan(s.func, s.Gs, s.N, s.Dp);
+  return s.Dp <= 256 && r.bytes <= kBFRunMax && r.threads <= bf_run_threads(r.R);
 }
 
 template <int FUNC>
 void launch_bf_run_f(const BFDev& s, int n_fit, int flush, hipStream_t st) {
-  const BFRunPlan r = bf_run_plan(s.Gs, s.N, s.Dp);
+  const BFRunPlan r = bf_run_plan(s.func, s.Gs, s.N, s.Dp);
   const dim3 grid(s.S), blk(r.threads);
   // Griewank's last rounding: swarms that this path has always run keep two
   const size_t nS = (size_t)s.Gs * s.N;
@@ -650,7 +663,7 @@ void launch_bf_run_f(const BFDev& s, int n_fit, int flush, hipStream_t st) {
   else if (r.R == 2)
     hipLaunchKernelGGL((bf_run_kernel<FUNC, 2>), grid, blk, r.bytes, st, s, n_fit, flush, r.L, r.ahead, fused);
   else
-    hipLaunchKernelGGL((bf_run_kernel<FUNC, 3>), grid, blk, r.bytes, st, s, n_fit, flush, r.L, r.ahead, fused);
+    hipLaunchKernelGGL((bf_run_kernel<FUNC, bf_run_many(FUNC)>), grid, blk, r.bytes, st, s, n_fit, flush, r.L, r.ahead, fused);
 }
 
 // n_fit evaluated iterations (then a flush move when flush) of every swarm,
