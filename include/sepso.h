@@ -385,9 +385,15 @@ typedef struct sepso_bf_cfg {
   uint64_t seed;
   int32_t swarms;                /* S independent swarms; 0 or 1 = one */
   int32_t path;                  /* 0: a swarm of rows of D <= 256 whose best rows (two copies)
-                                    and random factors fit in 64 KiB of LDS runs each call's iterations in one launch, one
-                                    workgroup per swarm; 1: always two launches per
-                                    iteration.  Both give bit-identical results. */
+                                    and random factors fit in 64 KiB of LDS, with G*N*lanes <=
+                                    3072 (lanes: the power of two >= D/4), runs each call's
+                                    iterations in one launch, one workgroup per swarm; 1:
+                                    always two launches per iteration.  Both give bit-identical
+                                    results, but for Griewank where 16*Q*(3*G*N + G) + 28*G*N +
+                                    40*G <= 65536 (Q = ceil(D/4)): there path 0 rounds the
+                                    cosines' product before subtracting it and path 1 does not,
+                                    a difference of at most 2^-25 in a value before its last
+                                    rounding. */
 } sepso_bf_cfg;
 
 /* Host views (any pointer may be NULL), with G_all = S*G groups: X, V, P:

@@ -94,11 +94,6 @@ __device__ __forceinline__ float wave_sum(float x) {
   for (int m = 32; m > 0; m >>= 1) x += __shfl_xor(x, m);
   return x;
 }
-__device__ __forceinline__ float wave_prod(float x) {
-#pragma unroll
-  for (int m = 32; m > 0; m >>= 1) x *= __shfl_xor(x, m);
-  return x;
-}
 
 // One coordinate's move (Eq.(7)-(8)) and one lane's four function terms:
 // shared by the stepwise and the whole-run kernels, so that both compute the
@@ -141,6 +136,15 @@ __device__ __forceinline__ void bf_terms(const float (&xv)[4], float prev, int e
       }
     }
   }
+}
+
+// Griewank's value from its sum and the product's last two factors: 1 + sum -
+// prod * last, rounded once (a fused multiply-add) or with the product rounded
+// by itself first.
+__device__ __forceinline__ float griewank_value(float sum, float prod, float last, bool once) {
+  float whole = prod * last;
+  asm("" : "+v"(whole));  // rounded: not contracted into the subtraction
+  return once ? fmaf(-prod, last, 1.f + sum) : 1.f + sum - whole;
 }
 
 template <int FUNC, bool FIT>
@@ -226,7 +230,11 @@ __global__ __launch_bounds__(256) void bf_iter_kernel(BFDev s) {
   }
   if (!FIT) return;
   float fv = wave_sum(acc);
-  if (FUNC == BF_GRIEWANK) fv = 1.f + fv - wave_prod(prod);
+  if (FUNC == BF_GRIEWANK) {
+#pragma unroll
+    for (int m = 32; m > 1; m >>= 1) prod *= __shfl_xor(prod, m);
+    fv = griewank_value(fv, prod, __shfl_xor(prod, 1), true);
+  }
   if (!(fabsf(fv) <= 3.402823466e38f)) fv = INFINITY;
   const bool imp = fv < s.Pf[i];
   if (lane == 0) {
@@ -329,7 +337,8 @@ __global__ __launch_bounds__(256) void bf_best_kernel(BFDev s, float* out) {
 // its iterations in one launch, one workgroup per swarm: the stepwise
 // kernels' move, evaluation, Pbest and bests in the same order and arithmetic
 // (bf_move, bf_terms, the same wave butterflies), so the results are
-// bit-identical.  The control word is read here and advanced by bf_ctl_kernel
+// bit-identical, but for one rounding of Griewank's value in the smaller swarms
+// (griewank_rounds_twice).  The control word is read here and advanced by bf_ctl_kernel
 // afterwards (every workgroup reads it unchanged).
 
 // Particles per lane group past two, and the most threads of a workgroup with R
@@ -444,7 +453,7 @@ __device__ __forceinline__ uint64_t min_shfl(uint64_t k, int m) {
 // and one thread scanning each group's Pbest it was 3.6).
 template <int FUNC, int R>
 __global__ __launch_bounds__(bf_run_threads(R)) void
-bf_run_kernel(BFDev s, int n_fit, int flush, int L, int ahead, int fused) {
+bf_run_kernel(BFDev s, int n_fit, int flush, int L, int ahead, int once) {
   extern __shared__ float4 s_dyn4[];
   const int sw = blockIdx.x, t = threadIdx.x, B = blockDim.x;
   const int Gs = s.Gs, N = s.N, D = s.D, Q = s.Dp / 4, nS = Gs * N, g0 = sw * Gs;
@@ -562,13 +571,8 @@ bf_run_kernel(BFDev s, int n_fit, int flush, int L, int ahead, int fused) {
         bf_terms<FUNC>(xv, prev, row[r] ? e : D, D, acc, prod);
         float f = seg_reduce(acc, L, [](float a, float b) { return a + b; });
         if (FUNC == BF_GRIEWANK) {
-          // the last factor and the subtraction with one rounding, as the
-          // stepwise kernel has them, or with two
           prod = seg_reduce<2>(prod, L, [](float a, float b) { return a * b; });
-          const float last = L > 1 ? lane_xor<1>(prod) : 1.f;
-          float whole = prod * last;
-          asm("" : "+v"(whole));  // rounded: not contracted into the subtraction
-          f = fused ? fmaf(-prod, last, 1.f + f) : 1.f + f - whole;
+          f = griewank_value(f, prod, L > 1 ? lane_xor<1>(prod) : 1.f, once);
         }
         if (!(fabsf(f) <= 3.402823466e38f)) f = INFINITY;
         fv[r] = f;
@@ -651,19 +655,28 @@ bool bf_run_fits(const BFDev& s) {
   return s.Dp <= 256 && r.bytes <= kBFRunMax && r.threads <= bf_run_threads(r.R);
 }
 
+// The swarms whose Griewank value the one-launch run takes with the product
+// rounded by itself, where two launches per iteration round once: three copies
+// of the rows, the groups' best rows and 28 and 40 bytes per particle and group
+// within 64 KiB (80 x 30: 43 KB).  Either rounding is right, a run's course
+// depends on it, and swarms keep the one that their seed's results were made
+// with: these fitted one workgroup when the whole swarm lay in its LDS.
+bool griewank_rounds_twice(size_t Gs, size_t N, size_t Q) {
+  const size_t nS = Gs * N;
+  return 16 * (3 * nS * Q + Gs * Q) + 28 * nS + 40 * Gs <= 64 * 1024;
+}
+
 template <int FUNC>
 void launch_bf_run_f(const BFDev& s, int n_fit, int flush, hipStream_t st) {
   const BFRunPlan r = bf_run_plan(s.func, s.Gs, s.N, s.Dp);
   const dim3 grid(s.S), blk(r.threads);
-  // Griewank's last rounding: swarms that this path has always run keep two
-  const size_t nS = (size_t)s.Gs * s.N;
-  const int fused = 16 * (3 * nS * r.Q + (size_t)s.Gs * r.Q) + 4 * (7 * nS + 10 * (size_t)s.Gs) > 64 * 1024;
+  const int once = !griewank_rounds_twice(s.Gs, s.N, r.Q);
   if (r.R == 1)
-    hipLaunchKernelGGL((bf_run_kernel<FUNC, 1>), grid, blk, r.bytes, st, s, n_fit, flush, r.L, r.ahead, fused);
+    hipLaunchKernelGGL((bf_run_kernel<FUNC, 1>), grid, blk, r.bytes, st, s, n_fit, flush, r.L, r.ahead, once);
   else if (r.R == 2)
-    hipLaunchKernelGGL((bf_run_kernel<FUNC, 2>), grid, blk, r.bytes, st, s, n_fit, flush, r.L, r.ahead, fused);
+    hipLaunchKernelGGL((bf_run_kernel<FUNC, 2>), grid, blk, r.bytes, st, s, n_fit, flush, r.L, r.ahead, once);
   else
-    hipLaunchKernelGGL((bf_run_kernel<FUNC, bf_run_many(FUNC)>), grid, blk, r.bytes, st, s, n_fit, flush, r.L, r.ahead, fused);
+    hipLaunchKernelGGL((bf_run_kernel<FUNC, bf_run_many(FUNC)>), grid, blk, r.bytes, st, s, n_fit, flush, r.L, r.ahead, once);
 }
 
 // n_fit evaluated iterations (then a flush move when flush) of every swarm,
