@@ -715,15 +715,29 @@ bool frame_plan(const sepso_batch* b, FrameLaunch* f) {
   return 1.05 * std::max(longest, wg) < 11.0 + launches;
 }
 
+// Whether iteration k ends with an online outer step of some instance.
+bool outer_step_due(const sepso_batch* b, int k) {
+  return std::any_of(b->desc.begin(), b->desc.end(),
+                     [&](const InstDesc& d) { return d.hsef_every > 0 && (k + 1) % d.hsef_every == 0; });
+}
+
 // Whether a frame's iterations take one launch each, every block finding its
 // groups' bests from all blocks' candidates at its start, instead of two: a
 // launch less of latency against a second round of memory reads in every
 // block.  It pays while blocks are few (one planner of 8 x 170 particles, 136
 // blocks: 435-545 -> 390-500 us a frame; 8 x 4096, 781 blocks: 2% faster; 64
 // instances, 1088 blocks: even) and a thread has few candidates to look at (10
-// each, 323 blocks of 64 threads: 11% slower; 7 each: 3% faster).
+// each, 323 blocks of 64 threads: 11% slower; 7 each: 3% faster).  An online
+// outer step is a launch of its own here and part of the second launch there,
+// so it must not be due too often: at every fourth iteration or less (every
+// fourth or fifth: even to 20% faster; every third: 8 x 1024 particles 3%
+// slower; every second: 9% slower to 10% faster; every one: 5-22% slower).
 bool one_launch_plan(const sepso_batch* b) {
   if (b->buckets.size() != 1 || b->buckets[0].tune.seg_per_thread > 12) return false;
+  int tmax = 0, due = 0;
+  for (const InstDesc& d : b->desc) tmax = std::max(tmax, d.T);
+  for (int k = 0; k < tmax; ++k) due += outer_step_due(b, k);
+  if (4 * due > tmax) return false;
   const TileBucket& bk = b->buckets[0];
   const int B = bk.tune.block_threads;
   // the bests' static LDS comes on top
@@ -752,9 +766,7 @@ hipError_t enqueue_frame(sepso_batch* b, bool move) {
     for (int k = 0; k <= tmax && e == hipSuccess; ++k) {
       if (!launch_one(bk.pl, bk.tune.seg_per_thread, bk.n_blocks, bk.tune.block_threads, k, b->stream))
         e = hipErrorInvalidValue;
-      if (std::any_of(b->desc.begin(), b->desc.end(),
-                      [&](const InstDesc& d) { return d.hsef_every > 0 && (k + 1) % d.hsef_every == 0; }))
-        launch_hsef_one(bk.pl, k, b->stream);
+      if (outer_step_due(b, k)) launch_hsef_one(bk.pl, k, b->stream);
     }
   } else {
     for (int k = 0; k < tmax && e == hipSuccess; ++k)

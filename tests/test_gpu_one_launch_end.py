@@ -20,7 +20,8 @@ def test_every_block_ends_with_the_frame(n_inst, G, N, W, tune, T):
     from paper_2308_10169_amd import sepso
     maps = [I.dynamic_map(70 + i, S=300.0, n_static=40, n_moving=20, side=(4.0, 15.0)) for i in range(n_inst)]
     sws = [I.dynamic_swarm(m.scale, seed=9, instance=i, groups=G, particles=N, waypoints=W, iters=T - i % 7,
-                           at_mode=2 if i % 2 == 0 else 0, hsef_every=10) for i, m in enumerate(maps)]
+                           at_mode=2 if i % 2 == 0 else 0,
+                           hsef_every=4 if n_inst == 1 else 10) for i, m in enumerate(maps)]
     print(f"one launch end n={n_inst} {G}x{N}x{W} tune={tune}", flush=True)
     ref = []
     for m, sw in zip(maps, sws):
