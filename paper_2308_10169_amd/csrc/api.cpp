@@ -727,7 +727,11 @@ bool outer_step_due(const sepso_batch* b, int k) {
 // block.  It pays while blocks are few (one planner of 8 x 170 particles, 136
 // blocks: 435-545 -> 390-500 us a frame; 8 x 4096, 781 blocks: 2% faster; 64
 // instances, 1088 blocks: even) and a thread has few candidates to look at (10
-// each, 323 blocks of 64 threads: 11% slower; 7 each: 3% faster).  An online
+// each, 323 blocks of 64 threads: 11% slower; 7 each: 3% faster).  A block of
+// one wave also waits for the bests' rows it takes in after them, so there both
+// together may come to nine words each (8 x 170 particles, 62 waypoints, tile
+// (8, 64), 11 each: 569 -> 612 us; ten each: 1-4% slower; 8 or 9 each: 1-4%
+// faster; tiles of 128 and 256 threads gain 0-18% at up to 11).  An online
 // outer step is a launch of its own here and part of the second launch there,
 // so it must not be due too often: at every fourth iteration or less (every
 // fourth or fifth: even to 20% faster; every third: 8 x 1024 particles 3%
@@ -742,8 +746,10 @@ bool one_launch_plan(const sepso_batch* b) {
   const int B = bk.tune.block_threads;
   // the bests' static LDS comes on top
   if (iter_lds_bytes(bk.pl, B) + 2048 > 65536 || bk.n_blocks > 4 * kCUs) return false;
-  for (const InstDesc& d : b->desc)
-    if (d.n_blocks + d.G > d.slots || d.n_blocks * bk.pl.ngb_max > 8 * B) return false;
+  for (const InstDesc& d : b->desc) {
+    const int cands = d.n_blocks * bk.pl.ngb_max, rows = bk.pl.gb_floats;
+    if (d.n_blocks + d.G > d.slots || cands > 8 * B || (B == 64 && cands + rows > 9 * B + 8)) return false;
+  }
   return true;
 }
 
