@@ -682,6 +682,14 @@ hipError_t enqueue_iteration(sepso_batch* b, int flags, bool fork, hipEvent_t be
 // Measured, 8 x 32 particles of 20 waypoints and 4 rectangles: 7.7 us against
 // 12 for one instance, 8.1 against 24 for 256, 35 against 66 for 1024; with
 // 10 rectangles one instance takes 13 against 12 and keeps the two launches.
+//
+// A workgroup of one wave per SIMD cannot overlap its instructions: where the
+// paths meet most rectangles they take 4.8 ns each (3.3 us besides), and two
+// launches 4.3 ns on as many waves as the tile deals the rectangles over (9.9
+// us besides).  One particle, us per iteration against two launches: 50
+// rectangles, tile (4, 256), 2680 instructions, 15.3 and 12.7; 36, (8, 128),
+// 2850, 16.8 and 16.5; 28, (4, 256), 1690, 11.3 and 11.9; 28, (8, 128), 2330,
+// 14.2 and 15.1; 50, (4, 64), 2680, 16.6 and 22.6.
 bool frame_plan(const sepso_batch* b, FrameLaunch* f) {
   if (b->buckets.size() != 1) return false;
   const sepso_tune& tu = b->buckets[0].tune;
@@ -701,6 +709,7 @@ bool frame_plan(const sepso_batch* b, FrameLaunch* f) {
     const double insts = 350.0 + 20.0 * K + (5.0 * K + 25.0) * d.n_rects + 20.0 * K * d.n_cpolys;
     const int work = d.n_blocks * f->block, passes = (work + f->threads - 1) / f->threads;
     const double us = 3.0 + passes * ((f->threads + 255) / 256) * insts * 2.5e-3;
+    if (f->threads <= 256 && (4.8 - 4.3 / b->buckets[0].pl.rsplit) * 1e-3 * insts > 6.6) return false;
     longest = std::max(longest, us);
     wg += us / kCUs;
     launches += std::max(nP * 2.0 * d.W * 1e-3, work / 64.0 * insts * 0.5e-3) / kCUs;
