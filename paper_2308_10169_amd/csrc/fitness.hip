@@ -22,28 +22,31 @@ namespace sepso {
 namespace {
 
 constexpr int kFitVerts = 2560;  // vertices staged in LDS per pass (20 KiB)
-constexpr int kFitPolys = 768;   // polygons per pass (boxes 12 KiB, offsets 3 KiB)
-constexpr int kFitLong = 32;     // a polygon of more edges is walked by the whole wave
+constexpr int kFitPolys = 736;   // polygons per pass (boxes and words of 818 pieces 16 KiB)
+constexpr int kFitLong = 32;     // a polygon of more edges is cut into chains
+constexpr int kFitChain = 31;    // edges of a chain (32 vertices)
 constexpr int kFitMaxThreads = 512;
 
-// LDS of one block: staged vertices, polygon boxes and offsets, the long
-// polygons' list and its length, the block's path points with the crossings
-// and the length of the segment that starts at each, and a queue per wave.
-// At most 64 KiB (K * threads <= 1024, so ppr * (W + 2) <= 1536).
+// LDS of one block: staged vertices, boxes and words of the pieces (a piece is a
+// polygon, or a chain of a long one), two counts of pieces past the polygons',
+// the block's path points with the crossings and the length of the segment that
+// starts at each, and a queue per wave.  At most 64 KiB (K * threads <= 1024,
+// so ppr * (W + 2) <= 1536).
 struct FitLds {
-  int verts, polys, longs;                        // capacities
-  int box, ptr, lng, pts, cross, len, queue, bytes;  // byte offsets (vertices at 0)
+  int verts, polys, pieces;                          // capacities
+  int box, word, extra, pts, cross, len, queue, bytes;  // byte offsets (vertices at 0)
 };
 
 __host__ __device__ inline FitLds fit_lds(int n_polys, int n_vert, int threads, int n_pts) {
   FitLds l{};
   l.verts = n_vert < kFitVerts ? (n_vert + 1) & ~1 : kFitVerts;  // 16-byte aligned boxes after them
   l.polys = n_polys < kFitPolys ? n_polys : kFitPolys;
-  l.longs = kFitVerts / kFitLong < l.polys ? kFitVerts / kFitLong : l.polys;
+  // m vertices make ceil(m / kFitChain) - 1 < m / kFitChain pieces more than one
+  l.pieces = l.polys + l.verts / kFitChain;
   l.box = 8 * l.verts;
-  l.ptr = l.box + 16 * l.polys;
-  l.lng = l.ptr + 4 * (l.polys + 1);
-  l.pts = (l.lng + 4 * (l.longs + 1) + 7) & ~7;
+  l.word = l.box + 16 * l.pieces;
+  l.extra = l.word + 4 * l.pieces;
+  l.pts = (l.extra + 8 + 7) & ~7;
   l.cross = l.pts + 8 * n_pts;
   l.len = l.cross + 4 * n_pts;
   l.queue = l.len + 4 * n_pts;
@@ -81,15 +84,18 @@ __device__ __forceinline__ void push_near(uint32_t& w, float o, float r) {
 // The lines of 64 lanes meet different polygons (one in thirty of a dense
 // map), so the (segment, polygon) pairs to test go through a queue in LDS and
 // any lane takes any pair, 64 at a time; with a queue per lane half the lanes
-// sat idle (607 us on the large case below).  Vertices, boxes and offsets are
-// staged in LDS, by polygon ranges that fit when the map is larger; a polygon
-// of more than kFitLong edges is walked by the whole wave, from LDS or, when
-// it exceeds a pass by itself, from memory.
+// sat idle (607 us on the large case below).  Vertices, boxes and words are
+// staged in LDS, by polygon ranges that fit when the map is larger.  A polygon
+// of more than kFitLong edges goes in chains of kFitChain, each with a box of
+// its own like a polygon; one that exceeds a pass by itself, a pass at a time.
+// (Walked edge by edge by each wave, such polygons took up to 2.3 times what
+// testing every pair takes: a block's few waves wait on every edge in turn.)
 //
 // 32768 uniform paths of 64 waypoints on 600 polygons (2400 edges): 1803 -> 390
 // us a call; 1360 paths of 20 on 30 rectangles: 28.2 -> 8.5 us; 128 paths of 8
 // on 4 rectangles: 13.5 -> 8.2 us, of which the host's call and the launch are
-// most (before: every pair tested, three launches).
+// most; 8192 paths of 20 on 24 polygons of 100 edges: 257 -> 77 us; 32768 of 8
+// on one of 20000: 2042 -> 105 us (before: every pair tested, three launches).
 template <int K>
 __global__ __launch_bounds__(kFitMaxThreads) void fit_kernel(
     int n_polys, const int32_t* __restrict__ pptr, const float* __restrict__ verts, int n_vert,
@@ -102,14 +108,19 @@ __global__ __launch_bounds__(kFitMaxThreads) void fit_kernel(
   float* s_vf = reinterpret_cast<float*>(s_fit);
   const float2* s_v = reinterpret_cast<const float2*>(s_fit);
   float4* s_box = reinterpret_cast<float4*>(s_fit + lds.box);
-  int* s_ptr = reinterpret_cast<int*>(s_fit + lds.ptr);
-  int* s_long = reinterpret_cast<int*>(s_fit + lds.lng);  // [0] their number
+  // a piece's first vertex (12 bits), edges less one (5), and the vertex its last
+  // edge ends in (12: a closed polygon's first); kNoPiece: nothing to test
+  uint32_t* s_word = reinterpret_cast<uint32_t*>(s_fit + lds.word);
+  int* s_extra = reinterpret_cast<int*>(s_fit + lds.extra);  // of this pass and the next, in turn
+  constexpr uint32_t kNoPiece = 0x80000000u;
+  auto word = [](int first, int edges, int last) { return (uint32_t)(first | (edges - 1) << 12 | last << 17); };
   float2* s_pt = reinterpret_cast<float2*>(s_fit + lds.pts);
   int* s_cross = reinterpret_cast<int*>(s_fit + lds.cross);
   float* s_len = reinterpret_cast<float*>(s_fit + lds.len);
   uint32_t* s_queue = reinterpret_cast<uint32_t*>(s_fit + lds.queue) + 2 * (t - lane);
   const bool one_pass = n_vert <= lds.verts && n_polys <= lds.polys;
   auto offset = [&](int q) { return min(max(pptr[q], 0), n_vert); };  // inside whatever it holds
+  int pieces = 0, turn = 0;  // staged pieces; passes staged so far
 
   for (int rd = 0; rd < rounds; ++rd) {
     const int path0 = (blockIdx.x * rounds + rd) * ppr;
@@ -145,6 +156,7 @@ __global__ __launch_bounds__(kFitMaxThreads) void fit_kernel(
         s_len[pt[k]] = __builtin_amdgcn_sqrtf(fmaf(dx[k], dx[k], dy[k] * dy[k]));  // v_sqrt_f32, within 1 ulp
       }
     }
+    if (rd == 0 && t < 2) s_extra[t] = 0;
     __syncthreads();
 
     // the queue's pairs from `first` on, one per lane of the first n
@@ -153,27 +165,35 @@ __global__ __launch_bounds__(kFitMaxThreads) void fit_kernel(
       if (lane < n) {
         const uint32_t e = s_queue[first + lane];
         const int i = e & 2047u, q = e >> 11;
-        const int v0 = s_ptr[q], m = s_ptr[q + 1] - v0;
+        const uint32_t w = s_word[q];
         // a zero-length segment is near every box, also those that hold nothing to test
-        if (m < 1 || m > kFitLong) return;
+        if (w == kNoPiece) return;
+        const int v0 = w & 4095u, m = (w >> 12 & 31u) + 1, last = w >> 17;
         const float2 a = s_pt[i], b = s_pt[i + 1];
         const float ddx = b.x - a.x, ddy = b.y - a.y, c = fmaf(ddy, a.x, -(ddx * a.y));
         // strict sides of vertex j, bit m - 1 - j
         uint32_t neg = 0, pos = 0;
-        for (int j = 0; j < m; ++j) {
-          const float2 v = s_v[v0 + j];
+        auto side = [&](const float2& v) {
           const float o = fmaf(ddx, v.y, fmaf(-ddy, v.x, c));
           neg = 2 * neg + (o < 0.f ? 1u : 0u);
           pos = 2 * pos + (o > 0.f ? 1u : 0u);
+        };
+        for (int j = 0; j < m; ++j) side(s_v[v0 + j]);
+        // the vertex that edge j starts in and, in the word's next place, the
+        // one it ends in: j + 1, or `last` (a closed polygon's vertex 0)
+        const uint32_t n0 = neg, p0 = pos;
+        if (last == v0) {
+          neg = (neg << 1) | (neg >> (m - 1));
+          pos = (pos << 1) | (pos >> (m - 1));
+        } else {
+          side(s_v[last]);
         }
-        // edge j joins vertices j and j + 1 (the last and vertex 0)
-        auto next = [&](uint32_t w) { return (w << 1) | (w >> (m - 1)); };
-        uint32_t st = ((neg & next(pos)) | (pos & next(neg))) & (0xffffffffu >> (32 - m));
+        uint32_t st = ((n0 & pos) | (p0 & neg)) & (0xffffffffu >> (32 - m));
         int n_cross = 0;
         while (st) {
           const int bit = 31 - __clz(st), j = m - 1 - bit;
           st ^= 1u << bit;
-          const float2 g = s_v[v0 + j], h = s_v[v0 + (bit == 0 ? 0 : j + 1)];
+          const float2 g = s_v[v0 + j], h = s_v[bit == 0 ? last : v0 + j + 1];
           const float ex = h.x - g.x, ey = h.y - g.y, ce = fmaf(ex, g.y, -(ey * g.x));
           const float o3 = fmaf(ex, a.y, fmaf(-ey, a.x, -ce));
           const float o4 = fmaf(ex, b.y, fmaf(-ey, b.x, -ce));
@@ -182,27 +202,12 @@ __global__ __launch_bounds__(kFitMaxThreads) void fit_kernel(
         if (n_cross) atomicAdd(&s_cross[i], n_cross);
       }
     };
-    // crossings of segment k with the edges of a long polygon
-    auto whole = [&](auto v, int m, int k) {
-      float2 a = v(0);
-      float o1 = fmaf(dx[k], a.y, fmaf(-dy[k], a.x, nc[k]));
-      int c = 0;
-      for (int j = 1; j <= m; ++j) {
-        const float2 b = v(j == m ? 0 : j);
-        const float ex = b.x - a.x, ey = b.y - a.y, ce = fmaf(ex, a.y, -(ey * a.x));
-        const float o2 = fmaf(dx[k], b.y, fmaf(-dy[k], b.x, nc[k]));
-        const float o3 = fmaf(ex, py[k], fmaf(-ey, px[k], -ce));
-        const float o4 = fmaf(ex, qy[k], fmaf(-ey, qx[k], -ce));
-        c += (opposite(o1, o2) && opposite(o3, o4)) ? 1 : 0;
-        o1 = o2;  // the next edge starts where this one ends
-        a = b;
-      }
-      if (c && tol[k] > 0.f) atomicAdd(&s_cross[pt[k]], c);
-    };
 
+    int done = 0;  // edges of polygon q0 behind us, when it exceeds a pass by itself
     for (int q0 = 0; q0 < n_polys;) {
-      // polygons q0 .. q1 - 1 of this pass, their vertices from v0 on
-      int q1 = n_polys;
+      // this pass: polygons q0 .. q1 - 1, their vertices from v0 on, or the chain
+      // of `chain` edges of q0 from its vertex `done` on
+      int q1 = n_polys, chain = 0;
       const int v0 = one_pass ? 0 : offset(q0);
       if (!one_pass) {  // the longest range that fits
         int lo = q0, hi = min(q0 + lds.polys, n_polys);
@@ -214,33 +219,50 @@ __global__ __launch_bounds__(kFitMaxThreads) void fit_kernel(
             hi = mid - 1;
         }
         q1 = lo;
-        if (q1 == q0) {  // one polygon larger than a pass, read from memory
-          const int m = offset(q0 + 1) - v0;
-          const float* g = verts + 2 * (int64_t)v0;
-#pragma unroll
-          for (int k = 0; k < K; ++k)
-            whole([&](int j) { return make_float2(g[2 * (int64_t)j], g[2 * (int64_t)j + 1]); }, m, k);
-          ++q0;
-          continue;
-        }
+        if (q1 == q0) chain = min(offset(q0 + 1) - v0 - done, lds.verts - 1);
       }
-      const int np = q1 - q0;
       if (!one_pass || rd == 0) {
         if (!one_pass) __syncthreads();  // the last pass has been read
-        const int nv = one_pass ? n_vert : max(offset(q1) - v0, 0);
-        for (int i = t; i < 2 * nv; i += B) s_vf[i] = verts[2 * (int64_t)v0 + i];
-        for (int i = t; i <= np; i += B) s_ptr[i] = min(max(offset(q0 + i) - v0, 0), nv);
-        if (t == 0) s_long[0] = 0;
+        int* extra = s_extra + (turn & 1);
+        const float* g = verts + 2 * (int64_t)(v0 + done);
+        if (chain == 0) {
+          const int np = q1 - q0, nv = one_pass ? n_vert : max(offset(q1) - v0, 0);
+          for (int i = t; i < 2 * nv; i += B) s_vf[i] = g[i];
+          for (int i = t; i < np; i += B) {
+            const int a = min(max(pptr[q0 + i] - v0, 0), nv), m = min(max(pptr[q0 + i + 1] - v0, 0), nv) - a;
+            s_word[i] = m < 1 ? kNoPiece : m <= kFitLong ? word(a, m, a) : word(a, kFitChain, a + kFitChain);
+            if (m > kFitLong) {  // the other chains, after the polygons
+              const int more = (m - 1) / kFitChain;
+              int at = np + atomicAdd(extra, more);
+              for (int j = 1; j <= more; ++j, ++at) {
+                const int s = j * kFitChain, e = min(m, s + kFitChain);
+                if (at < lds.pieces) s_word[at] = word(a + s, e - s, e == m ? a : a + e);
+              }
+            }
+          }
+        } else {
+          // a chain's vertices, its last edge's end (the polygon's first vertex
+          // after its last) among them
+          const bool closes = v0 + done + chain == offset(q0 + 1);
+          for (int i = t; i < 2 * chain; i += B) s_vf[i] = g[i];
+          if (t < 2) s_vf[2 * chain + t] = closes ? verts[2 * (int64_t)v0 + t] : g[2 * chain + t];
+          for (int i = t; i * kFitChain < chain; i += B) {
+            const int s = i * kFitChain, e = min(chain, s + kFitChain);
+            s_word[i] = word(s, e - s, e);
+          }
+        }
         __syncthreads();
-        for (int i = t; i < np; i += B) {
-          const int a = s_ptr[i], m = s_ptr[i + 1] - a;
+        // (more than there is room for only if the offsets are malformed)
+        pieces = chain ? (chain + kFitChain - 1) / kFitChain : min(q1 - q0 + *extra, lds.pieces);
+        if (t == 0) s_extra[(turn + 1) & 1] = 0;
+        ++turn;
+        for (int i = t; i < pieces; i += B) {
+          const uint32_t w = s_word[i];
           float4 b = make_float4(0.f, 0.f, -FLT_MAX, -FLT_MAX);  // nothing to test here
-          if (m > kFitLong) {
-            const int at = atomicAdd(&s_long[0], 1);
-            if (at < lds.longs) s_long[1 + at] = i;  // always, unless the offsets are malformed
-          } else if (m > 0) {
-            float x0 = s_v[a].x, x1 = x0, y0 = s_v[a].y, y1 = y0;
-            for (int j = 1; j < m; ++j) {
+          if (w != kNoPiece) {
+            const int a = w & 4095u, m = (w >> 12 & 31u) + 1, last = w >> 17;
+            float x0 = s_v[last].x, x1 = x0, y0 = s_v[last].y, y1 = y0;
+            for (int j = last == a ? 1 : 0; j < m; ++j) {
               const float2 v = s_v[a + j];
               x0 = fminf(x0, v.x);
               x1 = fmaxf(x1, v.x);
@@ -258,8 +280,8 @@ __global__ __launch_bounds__(kFitMaxThreads) void fit_kernel(
         __syncthreads();
       }
       int queued = 0;  // the wave's
-      for (int i0 = 0; i0 < np; i0 += 32) {
-        const int n = min(32, np - i0);
+      for (int i0 = 0; i0 < pieces; i0 += 32) {
+        const int n = min(32, pieces - i0);
         uint32_t near[K];
 #pragma unroll
         for (int k = 0; k < K; ++k) near[k] = 0;
@@ -302,13 +324,11 @@ __global__ __launch_bounds__(kFitMaxThreads) void fit_kernel(
         }
       }
       work_off(0, queued);
-      const int n_long = min(s_long[0], lds.longs);
-      for (int i = 0; i < n_long; ++i) {
-        const int q = s_long[1 + i], a = s_ptr[q], m = s_ptr[q + 1] - a;
-#pragma unroll
-        for (int k = 0; k < K; ++k) whole([&](int j) { return s_v[a + j]; }, m, k);
+      done += chain;
+      if (chain == 0 || v0 + done == offset(q0 + 1)) {
+        q0 = max(q1, q0 + 1);
+        done = 0;
       }
-      q0 = q1;
     }
 
     __syncthreads();
