@@ -25,6 +25,7 @@ constexpr int kFitVerts = 2560;  // vertices staged in LDS per pass (20 KiB)
 constexpr int kFitPolys = 736;   // polygons per pass (boxes and words of 818 pieces 16 KiB)
 constexpr int kFitLong = 32;     // a polygon of more edges is cut into chains
 constexpr int kFitChain = 31;    // edges of a chain (32 vertices)
+constexpr float kFitBig = 0x1p62f;
 constexpr int kFitMaxThreads = 512;
 
 // LDS of one block: staged vertices, boxes and words of the pieces (a piece is a
@@ -77,7 +78,9 @@ __device__ __forceinline__ void push_near(uint32_t& w, float o, float r) {
 // orientations (about 4 u (|dx| Y + |dy| X) each with u = 2^-24, X and Y the
 // largest coordinates; the margin is 16 u of it), so |o| > r means that the
 // edge-by-edge test would find every vertex strictly on one side and count
-// nothing: the counts are those of testing every pair, bit for bit.  Skipping
+// nothing: the counts are those of testing every pair, bit for bit.  (Segments
+// and boxes whose numbers pass kFitBig, where the products of both may leave the
+// range of a float, are near everything.)  Skipping
 // by the segment's own extent as well would need a tolerance that near-
 // parallel contacts break, so it is left out.
 //
@@ -149,6 +152,7 @@ __global__ __launch_bounds__(kFitMaxThreads) void fit_kernel(
       // the margin's share of the segment's own coordinates (and a floor far
       // above the rounding of subnormal values); idle lanes are near nothing
       tol[k] = active ? fmaf(0x1p-20f, fabsf(dx[k] * py[k]) + fabsf(dy[k] * px[k]), 1e-37f) : -1.f;
+      if (active && fmaxf(fabsf(dx[k]), fabsf(dy[k])) > kFitBig) tol[k] = INFINITY;
       if (active) {
         s_pt[pt[k]] = make_float2(px[k], py[k]);
         if (s == W) s_pt[pt[k] + 1] = make_float2(qx[k], qy[k]);
@@ -274,6 +278,7 @@ __global__ __launch_bounds__(kFitMaxThreads) void fit_kernel(
             b.y = 0.5f * y0 + 0.5f * y1;
             b.z = fmaf(fmaxf(x1 - b.x, b.x - x0), 1.f + 0x1p-19f, 0x1p-20f * fmaxf(fabsf(x0), fabsf(x1)));
             b.w = fmaf(fmaxf(y1 - b.y, b.y - y0), 1.f + 0x1p-19f, 0x1p-20f * fmaxf(fabsf(y0), fabsf(y1)));
+            if (fmaxf(fmaxf(fabsf(x0), fabsf(x1)), fmaxf(fabsf(y0), fabsf(y1))) > kFitBig) b.z = b.w = INFINITY;
           }
           s_box[i] = b;
         }
