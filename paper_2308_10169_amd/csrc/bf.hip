@@ -341,19 +341,19 @@ __global__ __launch_bounds__(256) void bf_best_kernel(BFDev s, float* out) {
 // (griewank_rounds_twice).  The control word is read here and advanced by bf_ctl_kernel
 // afterwards (every workgroup reads it unchanged).
 
-// Particles per lane group past two, and the most threads of a workgroup with R
-// of them.  A lane's registers (128 with 1024 threads) hold three particles'
-// state and one particle's temporaries, or two with Griewank's cosine, which
-// past two takes six on half the threads: its third made the loop spill.
+// Most threads of a workgroup with R particles per lane group.  A lane's
+// registers (128 with 1024 threads) hold three particles' state and one
+// particle's temporaries, or two with Griewank's cosine, which past two takes
+// five or six on half the threads: its third made the loop spill.
 // 12 x 30 particles of 18: 5.4 -> 5.3 us an iteration with Rastrigin (before:
-// three with spills), Griewank 7.3 -> 7.7; 5 x 8 of 137, Griewank 5.2 -> 7.4.
-constexpr int bf_run_many(int func) { return func == BF_GRIEWANK ? 6 : 3; }
+// three with spills), Griewank 7.3 -> 7.6 with six; 5 x 8 of 137, Griewank 5.2 ->
+// 6.2 with five, and a call of one iteration 30 -> 25 us (600 swarms 81 -> 56).
 constexpr int bf_run_threads(int R) { return R <= 3 ? 1024 : 512; }
 constexpr int kBFRunMax = 64 * 1024;  // LDS bytes
 
 struct BFRunPlan {
   int Q, L;          // float4 groups per row, lanes per particle (power of two >= Q)
-  int R, threads;    // particles per thread's lane group (1, 2 or bf_run_many), threads of the workgroup
+  int R, threads;    // particles per thread's lane group, threads of the workgroup
   int ahead;         // iterations whose random factors are drawn together
   size_t bytes;      // dynamic LDS
 };
@@ -364,7 +364,8 @@ inline BFRunPlan bf_run_plan(int func, int Gs, int N, int Dp) {
   r.L = 1;
   while (r.L < r.Q) r.L *= 2;
   const size_t nS = (size_t)Gs * N;
-  r.R = nS * r.L <= 1024 ? 1 : nS * r.L <= 2048 ? 2 : bf_run_many(func);
+  const int half = func == BF_GRIEWANK && nS * r.L > 2048;
+  r.R = (int)((nS * r.L + (half ? 511 : 1023)) / (half ? 512 : 1024));
   const size_t per = (nS + r.R - 1) / r.R;
   r.threads = (int)((per * r.L + 63) / 64 * 64);
   for (r.ahead = r.L < 8 ? r.L : 8;; r.ahead /= 2) {
@@ -551,7 +552,7 @@ bf_run_kernel(BFDev s, int n_fit, int flush, int L, int ahead, int once) {
 #pragma unroll
         for (int j = 0; j < 4; ++j)  // (past a row's end too: nothing reads those)
           xs[j] = bf_move(xs[j], vs[j], ps[j], gs[j], ts[j], w, c.x, c.y, c.z, vmax[r], s.lo, s.hi);
-        if (R > 2) __builtin_amdgcn_sched_barrier(0);  // one particle's temporaries at a time
+        if (R == 3) __builtin_amdgcn_sched_barrier(0);  // one particle's temporaries at a time
       }
       --drawn;
     }
@@ -584,7 +585,7 @@ bf_run_kernel(BFDev s, int n_fit, int flush, int L, int ahead, int once) {
         // (an infinite or NaN Pbest is no group's best)
         if (own[r] && pf[r] < INFINITY)
           atomicMin(reinterpret_cast<unsigned long long*>(sB + words + grp[r]), bf_key(pf[r], id[r]));
-        if (R > 2) __builtin_amdgcn_sched_barrier(0);
+        if (R == 3) __builtin_amdgcn_sched_barrier(0);
       }
       __syncthreads();
       // total best: lowest fitness, lowest group and index on ties
@@ -652,7 +653,7 @@ __global__ void bf_ctl_kernel(BFDev s, int n_fit, int flush) {
 // or more for the two launches.
 bool bf_run_fits(const BFDev& s) {
   const BFRunPlan r = bf_run_plan(s.func, s.Gs, s.N, s.Dp);
-  return s.Dp <= 256 && r.bytes <= kBFRunMax && r.threads <= bf_run_threads(r.R);
+  return s.Dp <= 256 && r.bytes <= kBFRunMax && (int64_t)s.Gs * s.N * r.L <= 3 * 1024;
 }
 
 // The swarms whose Griewank value the one-launch run takes with the product
@@ -666,17 +667,35 @@ bool griewank_rounds_twice(size_t Gs, size_t N, size_t Q) {
   return 16 * (3 * nS * Q + Gs * Q) + 28 * nS + 40 * Gs <= 64 * 1024;
 }
 
+// Whether a call of one iteration takes the two launches all the same: Griewank
+// with five or six particles per lane, where filling the registers costs more
+// than it saves unless there is much to evaluate (us a call, one launch and
+// two: 5 x 8 x 137 25.5 and 23.5, 600 swarms 56 and 48; 12 x 30 x 18 26.6 and
+// 23.6, 32 swarms 28.7 and 31.3, 600 swarms 62 and 199; 8 x 10 x 100, 600 swarms
+// 60 and 68).  Two iterations: one launch, 32 and 33 at the least.
+bool bf_run_fills_late(const BFDev& s) {
+  const BFRunPlan r = bf_run_plan(s.func, s.Gs, s.N, s.Dp);
+  return r.R > 3 && !griewank_rounds_twice(s.Gs, s.N, r.Q) && (s.G * s.N <= 4096 || s.Gs * s.N <= 48);
+}
+
 template <int FUNC>
 void launch_bf_run_f(const BFDev& s, int n_fit, int flush, hipStream_t st) {
   const BFRunPlan r = bf_run_plan(s.func, s.Gs, s.N, s.Dp);
   const dim3 grid(s.S), blk(r.threads);
   const int once = !griewank_rounds_twice(s.Gs, s.N, r.Q);
+#define RUN(R) \
+  hipLaunchKernelGGL((bf_run_kernel<FUNC, R>), grid, blk, r.bytes, st, s, n_fit, flush, r.L, r.ahead, once)
   if (r.R == 1)
-    hipLaunchKernelGGL((bf_run_kernel<FUNC, 1>), grid, blk, r.bytes, st, s, n_fit, flush, r.L, r.ahead, once);
+    RUN(1);
   else if (r.R == 2)
-    hipLaunchKernelGGL((bf_run_kernel<FUNC, 2>), grid, blk, r.bytes, st, s, n_fit, flush, r.L, r.ahead, once);
+    RUN(2);
+  else if constexpr (FUNC != BF_GRIEWANK)
+    RUN(3);
+  else if (r.R <= 5)
+    RUN(5);
   else
-    hipLaunchKernelGGL((bf_run_kernel<FUNC, bf_run_many(FUNC)>), grid, blk, r.bytes, st, s, n_fit, flush, r.L, r.ahead, once);
+    RUN(6);
+#undef RUN
 }
 
 // n_fit evaluated iterations (then a flush move when flush) of every swarm,
@@ -811,7 +830,7 @@ sepso_status bf_usable(sepso_bf* b) {
 }
 
 sepso_status bf_run(sepso_bf* b, int32_t n) {
-  if (b->whole_run && n > 0) {
+  if (b->whole_run && n > 0 && !(n == 1 && bf_run_fills_late(b->dev))) {
     launch_bf_run(b->dev, n, 1, b->stream);
   } else {
     for (int k = 0; k < n; ++k) launch_bf_step(b->dev, true, b->stream);
