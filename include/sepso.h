@@ -263,7 +263,8 @@ sepso_status sepso_batch_plan(sepso_batch* b, int32_t n_frames, sepso_frame_resu
 /* State of instance i of a batch (same views as sepso_get_state). */
 sepso_status sepso_batch_get_state(sepso_batch* b, int32_t i, sepso_state* st);
 sepso_status sepso_batch_profile_step(sepso_batch* b, int32_t n, float* avg_ms);
-/* Choose seg_per_thread / block_threads by timing candidates on this batch;
+/* Choose seg_per_thread / block_threads by timing the first iterations of a
+ * frame under each candidate on this batch, launched as frames launch them;
  * the winner is applied to the batch and written to *best (may be NULL).
  * Afterwards the batch is as new: control blocks (random-stream positions,
  * frame index, previous plans) and hyper-parameters reset and the frame-0

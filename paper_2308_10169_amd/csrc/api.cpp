@@ -8,6 +8,7 @@
 #include <cstdio>
 #include <cstring>
 #include <string>
+#include <utility>
 #include <vector>
 
 #include "../../include/sepso.h"
@@ -724,6 +725,12 @@ bool frame_plan(const sepso_batch* b, FrameLaunch* f) {
   return 1.05 * std::max(longest, wg) < 11.0 + launches;
 }
 
+int max_iters(const sepso_batch* b) {
+  int tmax = 0;
+  for (auto& d : b->desc) tmax = std::max(tmax, d.T);
+  return tmax;
+}
+
 // Whether iteration k ends with an online outer step of some instance.
 bool outer_step_due(const sepso_batch* b, int k) {
   return std::any_of(b->desc.begin(), b->desc.end(),
@@ -747,8 +754,8 @@ bool outer_step_due(const sepso_batch* b, int k) {
 // slower; every second: 9% slower to 10% faster; every one: 5-22% slower).
 bool one_launch_plan(const sepso_batch* b) {
   if (b->buckets.size() != 1 || b->buckets[0].tune.seg_per_thread > 12) return false;
-  int tmax = 0, due = 0;
-  for (const InstDesc& d : b->desc) tmax = std::max(tmax, d.T);
+  int due = 0;
+  const int tmax = max_iters(b);
   for (int k = 0; k < tmax; ++k) due += outer_step_due(b, k);
   if (4 * due > tmax) return false;
   const TileBucket& bk = b->buckets[0];
@@ -762,31 +769,37 @@ bool one_launch_plan(const sepso_batch* b) {
   return true;
 }
 
+// Enqueue a frame's iterations, or the first `iters` of them (no more than the
+// longest instance has).
+hipError_t enqueue_iterations(sepso_batch* b, int iters) {
+  hipError_t e = hipSuccess;
+  FrameLaunch fl;
+  if (frame_plan(b, &fl)) {
+    const TileBucket& bk = b->buckets[0];
+    if (!launch_frame(bk.pl, bk.tune.seg_per_thread, fl, b->n, iters, b->stream)) e = hipErrorInvalidValue;
+  } else if (one_launch_plan(b)) {
+    // a launch more finds the last iteration's bests and ends the frame
+    const TileBucket& bk = b->buckets[0];
+    const int n = iters < max_iters(b) ? iters : iters + 1;
+    for (int k = 0; k < n && e == hipSuccess; ++k) {
+      if (!launch_one(bk.pl, bk.tune.seg_per_thread, bk.n_blocks, bk.tune.block_threads, k, b->stream))
+        e = hipErrorInvalidValue;
+      if (outer_step_due(b, k)) launch_hsef_one(bk.pl, k, b->stream);
+    }
+  } else {
+    for (int k = 0; k < iters && e == hipSuccess; ++k)
+      e = enqueue_iteration(b, STEP_FIT | STEP_FRAME, true);
+  }
+  return e;
+}
+
 // Enqueue one whole frame of every instance; the first error of the
 // enqueued work (launch errors included).
 hipError_t enqueue_frame(sepso_batch* b, bool move) {
   if (move) launch_geom(b->pl, b->n, 1, b->stream);
   if (b->lin) lin_enqueue_proposals(b->lin, b);
   launch_init(b->pl, init_blocks(b), -1, 1, b->stream);
-  int tmax = 0;
-  for (auto& d : b->desc) tmax = std::max(tmax, d.T);
-  hipError_t e = hipSuccess;
-  FrameLaunch fl;
-  if (frame_plan(b, &fl)) {
-    const TileBucket& bk = b->buckets[0];
-    if (!launch_frame(bk.pl, bk.tune.seg_per_thread, fl, b->n, tmax, b->stream)) e = hipErrorInvalidValue;
-  } else if (one_launch_plan(b)) {
-    // the last launch finds the bests of iteration tmax and ends the frame
-    const TileBucket& bk = b->buckets[0];
-    for (int k = 0; k <= tmax && e == hipSuccess; ++k) {
-      if (!launch_one(bk.pl, bk.tune.seg_per_thread, bk.n_blocks, bk.tune.block_threads, k, b->stream))
-        e = hipErrorInvalidValue;
-      if (outer_step_due(b, k)) launch_hsef_one(bk.pl, k, b->stream);
-    }
-  } else {
-    for (int k = 0; k < tmax && e == hipSuccess; ++k)
-      e = enqueue_iteration(b, STEP_FIT | STEP_FRAME, true);
-  }
+  hipError_t e = enqueue_iterations(b, max_iters(b));
   if (e == hipSuccess)
     e = hipMemcpyAsync(b->h_ctl, b->pl.ctl, sizeof(InstCtl) * b->n, hipMemcpyDeviceToHost,
                        b->stream);
@@ -797,21 +810,29 @@ hipError_t enqueue_frame(sepso_batch* b, bool move) {
   return e;
 }
 
+// What `enqueue` enqueues on the batch's stream, as an instantiated graph.
+template <class F>
+sepso_status capture(sepso_batch* b, F enqueue, hipGraphExec_t* out) {
+  hipGraph_t g = nullptr;
+  HIPCHK(b, hipStreamBeginCapture(b->stream, hipStreamCaptureModeThreadLocal));
+  const hipError_t eq = enqueue();
+  hipError_t e = hipStreamEndCapture(b->stream, &g);
+  if (eq != hipSuccess) {
+    if (g) (void)hipGraphDestroy(g);
+    return hip_fail(b, eq, "frame capture");
+  }
+  if (e != hipSuccess) return hip_fail(b, e, "hipStreamEndCapture");
+  e = hipGraphInstantiate(out, g, nullptr, nullptr, 0);
+  (void)hipGraphDestroy(g);  // the instantiated graph keeps what it needs
+  if (e != hipSuccess) return hip_fail(b, e, "hipGraphInstantiate");
+  return SEPSO_OK;
+}
+
 sepso_status run_frame(sepso_batch* b, bool move, float* ms) {
   const int m = move ? 1 : 0;
   if (!b->graph[m]) {
-    hipGraph_t g = nullptr;
-    HIPCHK(b, hipStreamBeginCapture(b->stream, hipStreamCaptureModeThreadLocal));
-    const hipError_t eq = enqueue_frame(b, move);
-    hipError_t e = hipStreamEndCapture(b->stream, &g);
-    if (eq != hipSuccess) {
-      if (g) (void)hipGraphDestroy(g);
-      return hip_fail(b, eq, "frame capture");
-    }
-    if (e != hipSuccess) return hip_fail(b, e, "hipStreamEndCapture");
-    e = hipGraphInstantiate(&b->graph[m], g, nullptr, nullptr, 0);
-    (void)hipGraphDestroy(g);  // the instantiated graph keeps what it needs
-    if (e != hipSuccess) return hip_fail(b, e, "hipGraphInstantiate");
+    const sepso_status st = capture(b, [&] { return enqueue_frame(b, move); }, &b->graph[m]);
+    if (st != SEPSO_OK) return st;
   }
   HIPCHK(b, hipEventRecord(b->ev0, b->stream));
   HIPCHK(b, hipGraphLaunch(b->graph[m], b->stream));
@@ -1247,29 +1268,71 @@ sepso_status restart(sepso_batch* b) {
 
 }  // namespace
 
-sepso_status sepso_autotune(sepso_batch* b, sepso_tune* best) {
-  sepso_status st = usable(b);
+// Device time of a frame's first `iters` iterations from the frame-0 swarm, as
+// frames run them under the present tile: one run after a first one, or the
+// shorter of two where a run is under a millisecond (small swarms' runs differ by
+// as much as their tiles do).
+static sepso_status time_iterations(sepso_batch* b, int iters, float* ms) {
+  hipGraphExec_t x = nullptr;
+  sepso_status st = capture(b, [&] { return enqueue_iterations(b, iters); }, &x);
   if (st != SEPSO_OK) return st;
-  const int Ks[] = {4, 8, 12, 16, 24};
-  const int Bs[] = {64, 128, 256};
-  sepso_tune win = b->tune;
+  *ms = INFINITY;
+  hipError_t e = hipSuccess;
+  for (int r = 0; r < 3 && !(r == 2 && *ms > 1.f) && e == hipSuccess; ++r) {
+    float t = 0.f;
+    st = restart(b);
+    if (st != SEPSO_OK) break;
+    e = hipEventRecord(b->ev0, b->stream);
+    if (e == hipSuccess) e = hipGraphLaunch(x, b->stream);
+    if (e == hipSuccess) e = hipEventRecord(b->ev1, b->stream);
+    if (e == hipSuccess) e = hipEventSynchronize(b->ev1);
+    if (e == hipSuccess) e = hipEventElapsedTime(&t, b->ev0, b->ev1);
+    if (r > 0) *ms = std::min(*ms, t);
+  }
+  (void)hipGraphExecDestroy(x);
+  if (e != hipSuccess) return hip_fail(b, e, "autotune");
+  return st;
+}
+
+// The fastest candidate by time_iterations, with Auto Truncation as the batch has
+// it now (the caller switches it off).  A fresh swarm's first iterations meet many
+// rectangles and rank the tiles otherwise than the later ones do, so up to 36 are
+// timed, as far as two milliseconds go, and twelve in any case.
+static sepso_status fastest_tile(sepso_batch* b, sepso_tune* win) {
   float win_ms = INFINITY;
-  for (int K : Ks)
-    for (int B : Bs) {
+  const int most = std::min(36, max_iters(b)), least = std::min(12, most);
+  float ms = 0.f;
+  set_single(b, b->tune);
+  sepso_status st = upload_tiles(b);
+  if (st == SEPSO_OK) st = time_iterations(b, least, &ms);
+  if (st != SEPSO_OK) return st;
+  const int iters = std::min<float>(most, std::max<float>(least, 2.f * least / ms));
+  for (int K : {4, 8, 12, 16, 24})
+    for (int B : {64, 128, 256}) {
       if (!tune_ok(K, B, b->desc)) continue;
       set_single(b, sepso_tune{K, B});
       st = upload_tiles(b);
-      if (st != SEPSO_OK) return st;
-      float ms = 0.f;
-      st = profile_batch(b, 1, &ms);  // warm-up
-      if (st != SEPSO_OK) return st;
-      st = profile_batch(b, 3, &ms);
+      if (st == SEPSO_OK) st = time_iterations(b, iters, &ms);
       if (st != SEPSO_OK) return st;
       if (ms < win_ms) {
         win_ms = ms;
-        win = b->tune;
+        *win = b->tune;
       }
     }
+  return SEPSO_OK;
+}
+
+sepso_status sepso_autotune(sepso_batch* b, sepso_tune* best) {
+  sepso_status st = usable(b);
+  if (st != SEPSO_OK) return st;
+  sepso_tune win = b->tune;
+  // every candidate runs the same iterations: where Auto Truncation ends a frame
+  // hangs on the last bits of a path's length, which the tile's order decides
+  std::vector<int32_t> at;
+  for (InstDesc& d : b->desc) at.push_back(std::exchange(d.at_mode, 0));
+  st = fastest_tile(b, &win);
+  for (int i = 0; i < b->n; ++i) b->desc[i].at_mode = at[i];
+  if (st != SEPSO_OK) return st;
   set_single(b, win);
   st = upload_tiles(b);
   if (st == SEPSO_OK) st = restart(b);
