@@ -379,12 +379,6 @@ sepso_status fit_check(int32_t n_polys, int32_t n_vert, int32_t n_paths, int32_t
   return SEPSO_OK;
 }
 
-// Threads per block, segments per thread and whole paths per block and round.
-// Many segments: 512 threads of two segments each (a box is read from LDS once
-// for both), a few rounds per block so that staging the map is paid once for
-// several thousand segments.  Few: the smallest block that holds whole paths
-// without leaving more than a quarter of its threads idle, one segment per
-// thread, so that the call spreads over as many CUs as it can.
 template <int K>
 void fit_launch(int threads, int n_polys, const int32_t* pptr, const float* verts, int n_vert,
                 const float* ends, const float* paths, int n_paths, int W, int rounds, float alpha,
@@ -397,6 +391,12 @@ void fit_launch(int threads, int n_polys, const int32_t* pptr, const float* vert
                      L, Q);
 }
 
+// Threads per block, segments per thread and whole paths per block and round.
+// Many segments: 512 threads of two segments each (a box is read from LDS once
+// for both), a few rounds per block so that staging the map is paid once for
+// several thousand segments.  Few: the smallest block that holds whole paths
+// without leaving more than a quarter of its threads idle, one segment per
+// thread, so that the call spreads over as many CUs as it can.
 sepso_status fit_run(int32_t n_polys, int32_t n_vert, const int32_t* d_pptr, const float* d_verts,
                      const float* d_ends, const float* d_paths, int32_t n_paths, int32_t W,
                      float alpha, int32_t beta, float* d_f, float* d_L, int32_t* d_Q, hipStream_t s) {

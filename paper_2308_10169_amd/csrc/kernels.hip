@@ -794,30 +794,7 @@ __device__ __forceinline__ void crossings(const Pools& pl, const InstDesc& d, fl
   }
 }
 
-// ---------------------------------------------------------------------------
-// Fused iteration over one block = ppb consecutive particles of an instance
-// (flat index g*N + n, possibly spanning groups; at most one particle per
-// thread).
-//
-//  A. previous iteration's update, elementwise and coalesced over the
-//     block's contiguous (particle, coordinate) range; new positions also
-//     go to LDS, where they stay for the whole launch.  Every global read
-//     the block needs -- its X, V, P range, the gbest rows of its groups and
-//     Tbest, the hyper-parameters, its particles' old Pbest fitness and the
-//     first chunk of obstacle records -- is issued before the first barrier,
-//     so the block waits on memory about once;
-//  B. a particle's W+1 segments are cut into C chunks of K; thread t takes
-//     chunk t / ppb of particle t mod ppb (slots past the last segment are
-//     masked out);
-//  C. crossings of the K segments with every obstacle edge: rectangles and
-//     convex polygons by their points' inside words (records through the
-//     scalar cache), other polygons edge by edge (records staged in LDS):
-//     one packed side word of the edge's end vertex against the K segment
-//     lines and one of the K+1 points against the edge line, crossing bits
-//     = both straddle;
-//  D. per-particle Q and L summed in chunk order (deterministic), fitness
-//     and Pbest; improved particles' positions go from LDS to P.
-// ---------------------------------------------------------------------------
+// ---- one-launch iterations: the blocks' candidates, the outer step ------------
 // Group of the e-th of per pairs a block may have, its slot in *slot; -1
 // past the block's groups (the slot is then the instance's first).
 __device__ __forceinline__ int cand_group(const InstDesc& d, int per, int e, int* slot) {
@@ -873,6 +850,30 @@ __global__ __launch_bounds__(256) void hsef_one_kernel(Pools pl, int it) {
   if (!s_stop) hsef_step(pl, d, ctl, s_gf);
 }
 
+// ---------------------------------------------------------------------------
+// Fused iteration over one block = ppb consecutive particles of an instance
+// (flat index g*N + n, possibly spanning groups; at most one particle per
+// thread).
+//
+//  A. previous iteration's update, elementwise and coalesced over the
+//     block's contiguous (particle, coordinate) range; new positions also
+//     go to LDS, where they stay for the whole launch.  Every global read
+//     the block needs -- its X, V, P range, the gbest rows of its groups and
+//     Tbest, the hyper-parameters, its particles' old Pbest fitness and the
+//     first chunk of obstacle records -- is issued before the first barrier,
+//     so the block waits on memory about once;
+//  B. a particle's W+1 segments are cut into C chunks of K; thread t takes
+//     chunk t / ppb of particle t mod ppb (slots past the last segment are
+//     masked out);
+//  C. crossings of the K segments with every obstacle edge: rectangles and
+//     convex polygons by their points' inside words (records through the
+//     scalar cache), other polygons edge by edge (records staged in LDS):
+//     one packed side word of the edge's end vertex against the K segment
+//     lines and one of the K+1 points against the edge line, crossing bits
+//     = both straddle;
+//  D. per-particle Q and L summed in chunk order (deterministic), fitness
+//     and Pbest; improved particles' positions go from LDS to P.
+// ---------------------------------------------------------------------------
 template <int K, int R, bool FIT, bool ONE = false>
 __device__ __forceinline__ void iteration(const Pools& pl, int flags, int it = 0) {
   // dynamic LDS: positions | obstacle records | Tbest and the gbest rows of
