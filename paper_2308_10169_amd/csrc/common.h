@@ -100,7 +100,6 @@ struct InstCtl {
   int32_t k;             // iterations with bests done in the current plan
   int32_t pending;       // iteration k's velocity/position update not applied yet
   int32_t done;          // the current frame has ended
-  int32_t ended;         // one-launch iterations: the launch that ended it (INT32_MAX while it runs)
   int32_t frame;         // frames planned so far (random stream position for inits)
   uint32_t ctr;          // counter of iteration k's update draws
   uint32_t epoch_ctr;    // outer-swarm steps taken (random stream position)
@@ -113,6 +112,7 @@ struct InstCtl {
   float res_cost, res_len;
   int32_t res_q, res_iters, res_trunc, use_learned;
   float hist[kHist];     // Tbest fitness after iterations 1..k (ring)
+  int32_t ended;         // one-launch iterations: the launch that ended the frame (INT32_MAX while it runs)
 };
 
 
@@ -144,8 +144,6 @@ struct Pools {
   EdgeRec* edges;    // general polygons' edges
   CPoly* cpolys;     // convex polygons
   float4* rects;     // axis-aligned rectangles (x0, y0, x1, y1), x0 < x1, y0 < y1
-  Cand* cand;        // one-launch iterations: the blocks' bests (kernels.hip)
-  float* cand_rows;  // their rows, two buffers
   float4* rect_c;    // their centres and half sides (xc, yc, w/2, h/2)
   int2* pkind;       // per polygon: (1 = rectangle / 2, 3 = convex, counter-clockwise or not / 0 = general, slot in its pool)
   float2* verts;
@@ -166,6 +164,10 @@ struct Pools {
   float* proposal;   // G*2W learned initial path per group (layout of gbest_pos)
   const int2* blk_tiles;  // fused-iteration block -> (instance, first particle)
   const int2* blk_init;   // init block -> (instance, first element)
+  // (last, so that the two-launch kernels read their arguments in the same
+  // groups with and without them)
+  Cand* cand;        // one-launch iterations: the blocks' bests (kernels.hip)
+  float* cand_rows;  // their rows, two buffers
 };
 
 // Evolution phase: the higher-level swarm (H-SEPSO) over whole lower-level
