@@ -449,8 +449,8 @@ __device__ __forceinline__ uint64_t min_shfl(uint64_t k, int m) {
 // next written to the other copy, and nobody reaches the one after before
 // every wave has come to the next barrier.  A group's word needs no clearing:
 // a particle's Pbest never rises, so older entries never win.
-// 32 swarms of 80 x 30, 1400 iterations of Rastrigin: 5.12 -> 1.63 ms a launch
-// (1.17 us per iteration; with the state in LDS, five barriers per iteration
+// 32 swarms of 80 x 30, 1400 iterations of Rastrigin: 5.12 -> 1.59 ms a launch
+// (1.13 us per iteration; with the state in LDS, five barriers per iteration
 // and one thread scanning each group's Pbest it was 3.6).
 template <int FUNC, int R>
 __global__ __launch_bounds__(bf_run_threads(R)) void

@@ -1343,8 +1343,8 @@ __global__ __launch_bounds__(256) void update_kernel(Pools pl, int flags) {
 // outer step -- in one launch with the swarm in LDS, where the two launches
 // per iteration of the kernels above cost a small swarm their latency (a chain
 // of memory round trips each) and its rows' way to memory and back.  Bound by
-// the CU's issue: about 1500 instructions per wave and iteration at 8 x 32
-// particles of 20 waypoints and 4 rectangles.
+// the CU's issue: about 2200 instructions per wave and iteration, 1360 of them
+// VALU, at 8 x 32 particles of 20 waypoints and 4 rectangles.
 //
 // The arithmetic and its order are those of iter_kernel and reduce_kernel:
 // the same chunks of K segments, the same blocks of ppb particles and so the
@@ -1359,8 +1359,8 @@ __global__ __launch_bounds__(256) void update_kernel(Pools pl, int flags) {
 // row of 2W floats apart, 64 lanes of a point fetch met on as few as 8).
 //
 // 256 instances of 8 x 32 particles, 20 waypoints, 4 rectangles: 8.1 us per
-// iteration (two launches: 24), 1360 VALU instructions per wave, issue 0.55 of
-// the SIMDs' cycles at the two waves each that one instance per CU gives.
+// iteration (two launches: 24), VALU issue 0.55 of the SIMDs' cycles at the two
+// waves each that one instance per CU gives.
 // ---------------------------------------------------------------------------
 __host__ __device__ inline int frame_row(int W) { return 2 * (W | 1); }
 
