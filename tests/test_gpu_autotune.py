@@ -32,14 +32,22 @@ def test_tuned_frame_is_near_the_best(n, G, N, W, rects):
            for i, m in enumerate(maps)]
     print(f"autotune n={n} {G}x{N}x{W} rects={rects}", flush=True)
     times = {}
+
+    def add(tune):
+        bp = sepso.BatchPlanner(maps, sws, tune=tune)
+        times[tune] = min(times.get(tune, np.inf), _frame_s(bp))
+        bp.close()
+
     for tune in itertools.product((4, 8, 12, 16, 24), (64, 128, 256)):
         if tune[0] * tune[1] <= 4096:
-            bp = sepso.BatchPlanner(maps, sws, tune=tune)
-            times[tune] = _frame_s(bp)
-            bp.close()
+            add(tune)
     bp = sepso.BatchPlanner(maps, sws)
     tune = bp.autotune()
     bp.close()
-    print(f"tuned {tune} {times[tune] * 1e6:.0f} us, best {min(times, key=times.get)} {min(times.values()) * 1e6:.0f} us",
+    best = min(times, key=times.get)
+    for _ in range(3):  # the two in turn, so that a slow spell of the host meets both
+        add(best)
+        add(tune)
+    print(f"tuned {tune} {times[tune] * 1e6:.0f} us, best {best} {times[best] * 1e6:.0f} us",
           flush=True)
-    assert times[tune] <= 1.125 * min(times.values())
+    assert times[tune] <= 1.125 * times[best]
